@@ -67,14 +67,22 @@ extern "C" {
 
 /* arithmetic of the two convolutions (the update is always FP32, the
  * log-likelihood and convergence sums always FP64) */
-#define EM_FP32        0    /* FP32 products, FP32 accumulation               */
+#define EM_FP32        0    /* products and sums of binary32 accuracy.  sr = 1,
+                               15 < K <= 43, frames of 16384 pixels and more,
+                               not served: on the matrix cores, each operand as
+                               the exact sum of three bf16 parts, six of their
+                               nine products (the others are below 2^-24 of the
+                               whole one), summed in FP32 in levels; measured
+                               error against binary64 is below that of the
+                               direct convolution, which computes all else     */
 #define EM_BF16_SPLIT  1    /* BF16 MFMA, image and PSF split into hi+lo,
                                three products (hi hi, hi lo, lo hi), FP32
                                accumulation.  K = 43, sr = 1, not served: when
                                every frame's PSF keeps at most 1/16 of its
                                mass outside the 21 kernel rows nearest the
-                               centre (checked at set-up), the taps on the
-                               other rows take the hi hi product alone       */
+                               centre (checked at set-up), the PSF's lo part
+                               enters on those rows alone, the image's on
+                               them and up to five rows beyond                */
 #define EM_FP16_SPLIT  2    /* FP16 MFMA: image operand in binary16 with a
                                power-of-two scale (per staged tile of x; for
                                the adjoint of a Gaussian iteration with sr = 1,
@@ -260,7 +268,9 @@ int em_destroy(em_ctx* ctx);
  * creates no em_ctx; the caller passes y, v, psf, x0 (or NULL for the flat
  * start) and x exactly as for em_init.  Results are those of em_init +
  * em_iterate with the default kernel variants.
- * Limits: EM_ENOMEM when em_workspace_bytes(p) > EM_NOALLOC_SCRATCH_BYTES.
+ * Limits: EM_ENOMEM when em_workspace_bytes(p) > EM_NOALLOC_SCRATCH_BYTES (an
+ * EM_FP32 problem whose matrix-core tables alone take it beyond runs the direct
+ * convolution instead).
  * One array per GPU: calls are serialised inside the library and each one
  * synchronises `stream` before returning, so the next call may reuse the
  * array; work of the caller that overlaps a call on the same GPU must not

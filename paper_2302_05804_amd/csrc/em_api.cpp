@@ -82,9 +82,29 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   g->precision = p->precision;
   g->weight_mode = p->weight_mode;
   g->nu = p->weight_mode == EM_W_STUDENT_T ? p->nu : 0.f;
+  // FP32 on the matrix cores: from frames of 128 x 128 pixels on (below, the
+  // tables of a frame, 432 KB, would be most of the workspace)
+  g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->sr == 1 && g->Nf >= 128 * 128;
   if ((int64_t)g->n * g->Nf > ((int64_t)1 << 40)) { *why = "problem too large"; return false; }
   if (g->Nl >= ((int64_t)1 << 31)) { *why = "latent image of 2^31 pixels or more"; return false; }
   return true;
+}
+
+// Frame groups of a cell kernel launch (one workgroup fills a compute unit): the
+// count whose rounds over the 256 compute units, times a workgroup's frames plus
+// `fixed` (its set-up, in frames), take the least time.
+static int cell_groups(int tiles, int n, double fixed, int most) {
+  int best = 1;
+  double cost = 1e300;
+  for (int g = 1; g <= std::min(n, most); ++g) {
+    const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
+    const double c = (double)cdiv((int64_t)tiles * groups, 256) * ((double)fpg + fixed);
+    if (c < 0.98 * cost) {
+      cost = c;
+      best = (int)groups;
+    }
+  }
+  return best;
 }
 
 Plan make_plan(const Geometry& g) {
@@ -100,12 +120,13 @@ Plan make_plan(const Geometry& g) {
     pl.fwd_tiles = (int)(cdiv(g.Wf, mfma2_fwd_tile_w(g.precision)) *
                          cdiv(g.Hf, mfma2_fwd_tile_h(g.precision)));
   else if (mf)
-    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w()) * cdiv(g.Hf, mfma_tile_h()));
+    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w()) * cdiv(g.Hf, mfma_tile_h(g)));
   else
     pl.fwd_tiles = (int)(cdiv(g.Wf, fwd_tile_w(g)) * cdiv(g.Hf, fwd_tile_h(g)));
   int fg = (int)std::min<int64_t>(g.n, cdiv(target, pl.fwd_tiles));
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
+  if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, g.n));
   if (uses_m2n(g)) pl.fwd_fpg = M2N_FPG;   // the frames are the products' N dimension
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
   pl.adj_variant = 0;
@@ -113,7 +134,7 @@ Plan make_plan(const Geometry& g) {
     pl.adj_tiles = (int)(cdiv(g.Wl, mfma2_adj_tile_w(g.precision)) *
                          cdiv(g.Hl, mfma2_adj_tile_h(g.precision)));
   else if (mf)
-    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w()) * cdiv(g.Hl, mfma_tile_h()));
+    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w()) * cdiv(g.Hl, mfma_tile_h(g)));
   else
     pl.adj_tiles = (int)(cdiv(g.Wl, adj_tile_w(g)) * cdiv(g.Hl, adj_tile_h(g)));
   if (pl.adj_tiles >= (mf ? target / 4 : target / 2)) {
@@ -123,6 +144,13 @@ Plan make_plan(const Geometry& g) {
     int ag = (int)std::min<int64_t>(g.n, cdiv(target, pl.adj_tiles));
     ag = std::max(ag, 1);
     pl.adj_fpg = (int)cdiv(g.n, ag);
+    pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
+  }
+  if (uses_cell(g)) {
+    // never more partial planes than the rule above holds, which the split forms'
+    // workspaces have always had
+    const int most = g.mc32 ? std::min(g.n, 16) : pl.adj_groups;
+    pl.adj_fpg = (int)cdiv(g.n, cell_groups(pl.adj_tiles, g.n, 0.3, most));
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
   }
   if (g.weight_mode == EM_W_LITERAL) {
@@ -190,7 +218,7 @@ Layout make_layout(const Geometry& g, const Plan& pl) {
   L.tab = take((size_t)g.n * g.KC * TAB_LD * sizeof(float));
   L.mtab_fwd = take(uses_mfma(g) ? mfma_table_bytes(g, 0) : 0);
   L.mtab_adj = take(uses_mfma(g) ? mfma_table_bytes(g, 1) : 0);
-  L.tune = take(uses_mfma(g) ? (size_t)g.Nl * sizeof(float) : 0);
+  L.tune = take(uses_mfma(g) && g.precision != EM_FP32 ? (size_t)g.Nl * sizeof(float) : 0);
   L.part_ll = take((size_t)std::max(pl.fwd_tiles * pl.fwd_groups, pl.prep_blocks) * sizeof(double));
   L.part_rc = take((size_t)2 * std::max(pl.adj_tiles, pl.upd_blocks) * sizeof(double));
   L.part_prep = take((size_t)3 * pl.prep_blocks * sizeof(double));
@@ -582,10 +610,12 @@ extern "C" {
 // which the caller has already sized.
 static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float* v,
                      const float* psf, const float* x0, float* x, void* workspace,
-                     size_t ws_bytes, void* stream, bool serving, bool check_workspace) {
+                     size_t ws_bytes, void* stream, bool serving, bool check_workspace,
+                     bool allow_mc32 = true) {
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
+  if (serving || !allow_mc32) g.mc32 = 0;
   if (g.weight_mode == EM_W_LITERAL && g.sr != 1)
     return fail(EM_ENOTSUP, "the typeset weighting is defined for sr = 1 only");
   const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
@@ -633,9 +663,6 @@ static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float
     return fail(EM_EDEVICE, "prep: %s", hipGetErrorString(e));
   if ((e = launch_psf_tables(g, psf, c->tab, c->counters + 4, c->stream)) != hipSuccess)
     return fail(EM_EDEVICE, "psf tables: %s", hipGetErrorString(e));
-  if (uses_mfma(g) &&
-      (e = launch_mfma_tables(g, psf, c->mtab_fwd, c->mtab_adj, c->stream)) != hipSuccess)
-    return fail(EM_EDEVICE, "mfma tables: %s", hipGetErrorString(e));
   if (uses_r16(g) && (e = launch_r16_setup(g, c->u, psf, c->r16, c->r16_umax, c->r16_fsum,
                                            c->stream)) != hipSuccess)
     return fail(EM_EDEVICE, "r16 planes: %s", hipGetErrorString(e));
@@ -651,6 +678,10 @@ static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float
       return fail(EM_EDEVICE, "band check: %s", hipGetErrorString(e));
     c->pl.lo_band = over == 0 ? 1 : 0;
   }
+  if (uses_mfma(g) &&
+      (e = launch_mfma_tables(g, psf, c->mtab_fwd, c->mtab_adj, c->stream,
+                              c->pl.lo_band != 0)) != hipSuccess)
+    return fail(EM_EDEVICE, "mfma tables: %s", hipGetErrorString(e));
   if ((rc = adjoint_sum(c, c->r, c->B))) return rc;
   if ((e = launch_finalize_prep(c->part_prep, pl.prep_blocks, c->scalars, g.sr, c->stream)) !=
       hipSuccess)
@@ -825,6 +856,7 @@ int em_check_plan(const em_problem* p) {
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   for (int serving = 0; serving < 2; ++serving) {
+    if (serving) g.mc32 = 0;
     const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
     em_ctx c{};
     c.g = g;
@@ -903,7 +935,7 @@ int em_variant_count(void) { return mfma_variants(); }
 
 int em_set_variants(em_ctx* c, int32_t fwd_variant, int32_t adj_variant) {
   if (!c) return fail(EM_EINVAL, "ctx is NULL");
-  if (!uses_mfma(c->g)) return fail(EM_ENOTSUP, "variants exist for matrix-core precisions only");
+  if (c->g.precision == EM_FP32) return fail(EM_ENOTSUP, "variants exist for matrix-core precisions only");
   if (fwd_variant < 0 || fwd_variant >= mfma_variants() || adj_variant < 0 ||
       adj_variant >= mfma_variants())
     return fail(EM_EINVAL, "variant out of range");
@@ -916,7 +948,7 @@ int em_set_variants(em_ctx* c, int32_t fwd_variant, int32_t adj_variant) {
 int em_autotune(em_ctx* c, int32_t n_rep, int32_t* fwd_variant, int32_t* adj_variant,
                 double* ms) {
   if (!c) return fail(EM_EINVAL, "ctx is NULL");
-  if (!uses_mfma(c->g)) return fail(EM_ENOTSUP, "variants exist for matrix-core precisions only");
+  if (c->g.precision == EM_FP32) return fail(EM_ENOTSUP, "variants exist for matrix-core precisions only");
   if (n_rep < 1) return fail(EM_EINVAL, "n_rep must be >= 1");
   const int nv = mfma_variants();
   hipEvent_t e0, e1;
@@ -1205,7 +1237,12 @@ extern "C" int em_run_noalloc(const em_problem* p, const float* y, const float* 
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
-  const size_t need = make_layout(g, make_plan(g)).total;
+  size_t need = make_layout(g, make_plan(g)).total;
+  if (need > EM_NOALLOC_SCRATCH_BYTES && g.mc32) {
+    // without the matrix-core tables of the FP32 form
+    g.mc32 = 0;
+    need = make_layout(g, make_plan(g)).total;
+  }
   if (need > EM_NOALLOC_SCRATCH_BYTES)
     return fail(EM_ENOMEM,
                 "the problem needs %zu bytes of scratch; em_run_noalloc holds %zu (use em_init "
@@ -1225,7 +1262,7 @@ extern "C" int em_run_noalloc(const em_problem* p, const float* y, const float* 
   em_ctx c{};
   c.no_graph = true;   // eager launches: nothing is instantiated
   int rc = setup_job(&c, p, y, v, psf, x0, x, g_noalloc_ptr[dev], EM_NOALLOC_SCRATCH_BYTES,
-                     stream, false, false);
+                     stream, false, false, g.mc32 != 0);
   if (rc != EM_OK) return rc;
   if ((rc = em_iterate(&c, n_iter, loglik_trace)) != EM_OK) return rc;
   // the next call reuses the array: this one's kernels must be done

@@ -1,0 +1,345 @@
+// em_cell.h -- the 43 x 43 correlations of an EM iteration on the matrix cores
+// with 4 x 4 output cells (arXiv:2302.05804, Sec. 2, Eqs. (1)-(3)).
+//
+//     out[k][l] = sum_{a,b} g[a][b] in[k - 21 + a][l - 21 + b]
+//
+// One product of v_mfma_f32_16x16x32 takes the 16 outputs of a 4 x 4 cell (M),
+// 16 cells side by side in a row of cells (N: 64 output columns) and 32 values
+// of the cells' common window (K).  The window of a cell at (R, C) holds rows
+// R - 22 .. R + 25 and columns C - 22 .. C + 25: row d (0..47) and column k
+// (0..47) meet output (R + p, C + q) with tap (d - 1 - p, k - 1 - q).  The table
+// operand is that tap, zero outside the stamp:
+//     T[4p + q][d, k] = g[d - 1 - p][k - 1 - q].
+// 43 x 43 of the 46 x 48 window values that can be non-zero are taps: 84%, where a
+// row of 16 outputs (a one-dimensional Toeplitz operand of 43 + 15 values in
+// 64) is 67%: 106 products per 256 outputs and frame in the FP16 split form
+// instead of 128.
+//
+// Window row d of cell row R is image row R - 22 + d, and cell rows are 4 apart,
+// so with d = 4 j + E (class E = 0..3, j = 0..11) an image row 4 s + E serves
+// every cell row s - j.  A wave owns G consecutive cell rows; in class E it walks
+// over the image rows (step s reads row 4 s + E once from LDS) and multiplies
+// each by the table fragments of the j = s - g that its cell rows g need.  A
+// table fragment is read from LDS once per class and wave, at step j, and stays
+// in registers for the G steps that use it; so LDS serves 2 (image) fragments
+// per step and NB * 18 table fragments per class for up to 27 G products.
+//
+// Bound by the matrix cores (at the clock they hold under this load): 33 x 2048^2
+// in FP32 issues 3.7 PFLOP of products per launch, forward 2.24 ms = 1.64 PFLOP/s,
+// adjoint 2.48 ms (the r tile is staged anew for every frame); the direct FP32
+// convolution took 7.35 and 7.62 ms.  BF16 split on 33 x 1999 x 2111: forward 1.41
+// -> 1.18 ms, adjoint 2.17 -> 1.77 ms against one-dimensional Toeplitz operands.
+//
+// The 48 window columns of a row are one 32-wide chunk ("main") and a 16-wide
+// "tail"; the tails of rows j and j + 1 of a class (image rows 4 s + E and
+// 4 s + 4 + E) share one product.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <utility>
+
+#include "em_device.h"
+#include "em_internal.h"
+#include "em_mfma_common.h"
+
+namespace em {
+
+// f(0), f(1), ..., f(N - 1) with the index a compile-time constant
+#define EM_INLINE __attribute__((always_inline))
+template <class Fn, int... I>
+__device__ EM_INLINE inline void static_for_seq(std::integer_sequence<int, I...>, Fn&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class Fn>
+__device__ EM_INLINE inline void static_for(Fn&& f) {
+  static_for_seq(std::make_integer_sequence<int, N>{}, f);
+}
+
+constexpr int CELL_K = 43;        // kernel side
+constexpr int CELL_NJ = 12;       // window rows of one class
+constexpr int CELL_OFF = 22;      // window origin above / left of the cell
+constexpr int CELL_EXTRA = 44;    // image rows of a tile beyond its output rows
+
+// FP32 operands as three bf16 parts each, v = p0 + p1 + p2 exactly (24 significant
+// bits in three times 8), and the six products of weight 2^-16 and more; the
+// three left out are below 2^-24 of the product.  The largest product has an
+// accumulator of its own.
+template <>
+struct Prec<EM_FP32> {
+  using frag = bf16x8;
+  static constexpr int NA = 3, NB = 3, NP = 6;
+  static constexpr bool SCALED = false;
+  __device__ static constexpr int pa(int s) { return s == 1 || s == 3 ? 1 : s == 4 ? 2 : 0; }
+  __device__ static constexpr int pb(int s) { return s == 2 || s == 3 ? 1 : s == 5 ? 2 : 0; }
+  __device__ static inline f32x4 mma(const frag& a, const frag& b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+
+// Parts of two FP32 values, packed bf16 pairs.  EM_FP32: the first part of a value
+// above the largest bf16 is that one, not infinity.
+template <int PREC>
+__device__ inline void cell_split2(f32x2 v, uint32_t (&q)[Prec<PREC>::NB]) {
+  constexpr float M = 3.3895313892515355e38f;
+  f32x2 c = v;
+  if constexpr (PREC == EM_FP32)
+    c = f32x2{__builtin_amdgcn_fmed3f(v.x, -M, M), __builtin_amdgcn_fmed3f(v.y, -M, M)};
+  bf16x2 h = __builtin_convertvector(c, bf16x2);
+  q[0] = __builtin_bit_cast(uint32_t, h);
+#pragma unroll
+  for (int p = 1; p < Prec<PREC>::NB; ++p) {
+    const f32x2 f = __builtin_convertvector(h, f32x2);
+    v = f32x2{v.x - f.x, v.y - f.y};
+    h = __builtin_convertvector(v, bf16x2);
+    q[p] = __builtin_bit_cast(uint32_t, h);
+  }
+}
+
+// Which parts of the table a form holds and which products it takes.  BAND:
+// the parts beyond the first enter only on the 21 kernel rows within 10 of the
+// centre (window rows 12..35, j = 3..8), table rows outside them are zero.
+template <int PREC_, bool BAND_>
+struct CellForm {
+  using P = Prec<PREC_>;
+  using frag = typename P::frag;
+  static constexpr int PREC = PREC_;
+  static constexpr bool BAND = BAND_;
+  static constexpr int NA = P::NA, NB = P::NB, NP = P::NP;
+  // EM_FP32: sums in levels.  The largest product of each LEVEL rows of a class is
+  // summed apart from the other products and from the other rows, then the class,
+  // then the frame, so that the sums round less than the direct convolution's
+  // 43-term chains do
+  static constexpr bool LEVELS = PREC_ == EM_FP32;
+  static constexpr int LEVEL = 3;
+  // rows per unit (table fragments are staged in LDS one unit at a time, two
+  // units in LDS), units per class
+  static constexpr int JU = PREC_ == EM_FP32 ? 3 : 6;
+  static constexpr int NU = CELL_NJ / JU;
+  static constexpr bool has_main(int part, int j) { return part == 0 || !BAND || (j >= 3 && j <= 8); }
+  // a tail fragment of part `part` for rows j and j + 1
+  static constexpr bool has_tail(int part, int j) {
+    return (part == 0 || !BAND) ? (j % 2 == 0) : (j == 3 || j == 5 || j == 7);
+  }
+  // products of image part pa with table part pb.  The image's lo part meets the
+  // first table part, whose tails pair even rows: its tails cover rows 2..9.
+  static constexpr bool mul_main(int pa, int pb, int j) { return has_main(pa > pb ? pa : pb, j); }
+  static constexpr bool mul_tail(int pa, int pb, int j) {
+    return has_tail(pb, j) && (pa == 0 || !BAND || (j >= 2 && j <= 8));
+  }
+  // steps (of G cell rows) at which an image part beyond the first is used
+  static constexpr bool lo_step(int s, int G) { return !BAND || (s >= 2 && s <= 8 + G - 1); }
+  // position of a fragment in its unit (main fragments of every part, then tails)
+  static constexpr int slot(int part, int j, bool tail) {
+    const int j0 = j / JU * JU;
+    int s = 0;
+    for (int p = 0; p < NB; ++p)
+      for (int t = 0; t < 2; ++t)
+        for (int i = j0; i < j0 + JU; ++i) {
+          if (p == part && t == (tail ? 1 : 0) && i == j) return s;
+          if (t == 0 ? has_main(p, i) : has_tail(p, i)) ++s;
+        }
+    return s;
+  }
+  static constexpr int unit_frags(int u) {
+    int s = 0;
+    for (int p = 0; p < NB; ++p)
+      for (int i = u * JU; i < (u + 1) * JU; ++i) s += (has_main(p, i) ? 1 : 0) + (has_tail(p, i) ? 1 : 0);
+    return s;
+  }
+  static constexpr int max_unit() {
+    int m = 0;
+    for (int u = 0; u < NU; ++u) m = unit_frags(u) > m ? unit_frags(u) : m;
+    return m;
+  }
+  static constexpr int NFU = max_unit();              // fragments of a staged unit
+  static constexpr int UPF = 4 * NU;                   // units per frame
+  static constexpr int64_t FRAME = (int64_t)UPF * NFU * 64;   // 16-byte lanes per frame's table
+};
+
+// G cell rows per wave, WR x WC waves: (4 G WR) x (64 WC) outputs per workgroup.
+template <class F_, int G_, int WR_, int WC_>
+struct CellCfg {
+  using F = F_;
+  using frag = typename F::frag;
+  static constexpr int G = G_, WR = WR_, WC = WC_;
+  static constexpr int NW = WR * WC, NT = 64 * NW;
+  static constexpr int TH = 4 * G * WR, TW = 64 * WC;
+  static constexpr int ROWS = TH + CELL_EXTRA;   // image rows k0 - 22 .. k0 + TH + 21
+  static constexpr int COLS = TW + 48;            // image columns l0 - 22 .. l0 + TW + 25
+  static constexpr int PITCH = COLS;              // halves; rows start on 16-byte boundaries
+};
+
+// Eight consecutive 16-bit values of a staged plane (8-byte aligned).
+template <class F>
+__device__ inline F cell_ld8(const unsigned short* p) {
+  const uint2* q = reinterpret_cast<const uint2*>(p);
+  const uint2 a = q[0], b = q[1];
+  return __builtin_bit_cast(F, make_uint4(a.x, a.y, b.x, b.y));
+}
+
+// s_waitcnt vmcnt(N) lgkmcnt(0)
+template <int N>
+__device__ inline void cell_wait() {
+  static_assert(N >= 0 && N < 16, "low field of vmcnt");
+  __builtin_amdgcn_s_waitcnt(0x0070 | N);
+}
+
+// The table fragments in LDS: unit u of a class is staged in slot u & 1 (NU is
+// even, so the parity is the unit's own).  The slots are separate LDS arrays,
+// so that a read of one is not ordered behind the copies into the other.
+template <class F>
+struct CellSlots {
+  static_assert(F::NU % 2 == 0, "a unit's slot is known at compile time");
+  typename F::frag *s0, *s1;
+};
+
+// Copy unit `unit` (counted over the frames of the group) of a table into a slot;
+// the waves share its fragments (the last fragment is copied again where they do
+// not divide evenly: every wave issues the same number of copies, without a
+// branch, which the wait counts below rely on).  w: this wave, wave-uniform.
+template <class C>
+__device__ inline void cell_issue_unit(const typename C::frag* __restrict__ tab, int unit, int w,
+                                       typename C::frag* slot) {
+  using F = typename C::F;
+  const typename C::frag* src = tab + (int64_t)unit * F::NFU * 64 + (threadIdx.x & 63);
+#pragma unroll
+  for (int f = 0; f < F::NFU; f += C::NW) {
+    const int i = f + C::NW <= F::NFU ? f + w : min(f + w, F::NFU - 1);
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)(src + i * 64),
+                                     (__attribute__((address_space(3))) void*)(slot + i * 64), 16,
+                                     0, 0);
+  }
+}
+
+// Where a wave is in its table: units run over all frames of the group.
+template <class F>
+struct CellTab {
+  const typename F::frag* tab;
+  int unit, units, w;
+  CellSlots<F> slots;
+};
+
+// Work added at the unit boundaries of a frame (0 .. UPF - 1).  wait(b), before
+// the barrier of boundary b: at least this wave's copies of the next unit have
+// landed and its LDS reads are done.  after(b): behind the barrier, and behind
+// the issue of the copies of the unit after the next.
+struct CellNoHook {
+  __device__ void wait(int) const { cell_wait<0>(); }
+  __device__ void after(int) const {}
+};
+
+// Unit boundary: this wave's copies of the next unit have landed, every wave has
+// read the current one; then the slot just freed takes the unit after the next
+// (past the last one, the same unit again, so that every boundary issues the
+// same copies and needs no branch).
+template <class C, int U, class Hook>
+__device__ inline void cell_boundary(CellTab<typename C::F>& T, int boundary, Hook& hook) {
+  hook.wait(boundary);
+  __builtin_amdgcn_s_barrier();
+  __asm__ volatile("" ::: "memory");
+  cell_issue_unit<C>(T.tab, T.unit + 2 < T.units ? T.unit + 2 : T.unit, T.w,
+                     U % 2 == 0 ? T.slots.s0 : T.slots.s1);
+  ++T.unit;
+  hook.after(boundary);
+}
+
+// One class of one frame.  im, it: this lane's window start in the staged planes
+// for the main and the tail chunk (plane 0, window row E of the wave's first
+// cell row); plane: distance of the planes.
+template <class C, int E, class Hook>
+__device__ __attribute__((always_inline)) inline void cell_class(
+    const unsigned short* im, const unsigned short* it, int plane, CellTab<typename C::F>& T,
+    f32x4 (&acc)[C::G], Hook& hook) {
+  using F = typename C::F;
+  using frag = typename C::frag;
+  constexpr int G = C::G, NS = G + CELL_NJ - 1;
+  const int lane = threadIdx.x & 63;
+  frag Tm[F::NB][CELL_NJ], Tt[F::NB][CELL_NJ];
+  frag Am[2][F::NA], At[2][F::NA];
+  // rows 0 of class 0 and 47 of class 3 meet no tap in any output of a cell
+  constexpr auto main_used = [](int p, int j) {
+    return F::has_main(p, j) && !(E == 0 && j == 0) && !(E == 3 && j == CELL_NJ - 1);
+  };
+  auto load_T = [&](auto jc) EM_INLINE {
+    constexpr int j = jc;
+    const frag* sl = ((j / F::JU) % 2 == 0 ? T.slots.s0 : T.slots.s1) + lane;
+    static_for<F::NB>([&](auto pc) EM_INLINE {
+      constexpr int p = pc;
+      if constexpr (main_used(p, j)) Tm[p][j] = sl[F::slot(p, j, false) * 64];
+      if constexpr (F::has_tail(p, j)) Tt[p][j] = sl[F::slot(p, j, true) * 64];
+    });
+  };
+  // image fragments of step s; parts beyond the first only where a product needs them
+  auto load_A = [&](auto sc) EM_INLINE {
+    constexpr int s = sc;
+    static_for<F::NA>([&](auto pc) EM_INLINE {
+      constexpr int p = pc;
+      if constexpr (p == 0 || F::lo_step(s, G)) {
+        Am[s & 1][p] = cell_ld8<frag>(im + p * plane + 4 * s * C::PITCH);
+        if constexpr (s < NS - 1) At[s & 1][p] = cell_ld8<frag>(it + p * plane + 4 * s * C::PITCH);
+      }
+    });
+  };
+  f32x4 big[F::LEVELS ? G : 1], small[F::LEVELS ? G : 1], cls[F::LEVELS ? G : 1];
+  if constexpr (F::LEVELS)
+    static_for<G>([&](auto gc) EM_INLINE { big[gc] = small[gc] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+  load_T(std::integral_constant<int, 0>{});
+  load_A(std::integral_constant<int, 0>{});
+  static_for<NS>([&](auto sc) EM_INLINE {
+    constexpr int s = sc;
+    if constexpr (s > 0 && s % F::JU == 0 && s <= CELL_NJ)
+      cell_boundary<C, s / F::JU - 1>(T, E * F::NU + s / F::JU - 1, hook);
+    if constexpr (s > 0 && s < CELL_NJ && s % F::JU == 0) load_T(sc);
+    if constexpr (s + 1 < CELL_NJ && (s + 1) % F::JU != 0) load_T(std::integral_constant<int, s + 1>{});
+    if constexpr (s + 1 < NS) load_A(std::integral_constant<int, s + 1>{});
+    // keep these loads ahead of this step's products
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (F::LEVELS)
+      static_for<G>([&](auto gc) EM_INLINE {
+        constexpr int j = s - gc;
+        if constexpr (j > 0 && j < CELL_NJ && j % F::LEVEL == 0) {
+          if constexpr (j == F::LEVEL) cls[gc] = big[gc];
+          else cls[gc] += big[gc];
+          big[gc] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      });
+    static_for<F::NP>([&](auto kc) EM_INLINE {
+      constexpr int pa = F::P::pa(kc), pb = F::P::pb(kc);
+      static_for<G>([&](auto gc) EM_INLINE {
+        constexpr int g = G - 1 - gc, j = s - g;
+        if constexpr (j >= 0 && j < CELL_NJ) {
+          f32x4& sum = !F::LEVELS ? acc[g] : pa + pb == 0 ? big[F::LEVELS ? g : 0] : small[F::LEVELS ? g : 0];
+          if constexpr (F::mul_main(pa, pb, j) && main_used(pb, j))
+            sum = F::P::mma(Tm[pb][j], Am[s & 1][pa], sum);
+          if constexpr (F::mul_tail(pa, pb, j)) sum = F::P::mma(Tt[pb][j], At[s & 1][pa], sum);
+        }
+      });
+    });
+  });
+  if constexpr (F::LEVELS)
+    static_for<G>([&](auto gc) EM_INLINE {
+      acc[gc] += cls[gc] + (big[gc] + small[gc]);
+      // add now: sunk to the frame's end, the addends of every class would be spilled
+      __asm__ volatile("" : "+v"(acc[gc]));
+    });
+}
+
+// All classes of one frame into acc (one wave's G cell rows x 16 cells).  On
+// entry the frame's first unit is in its slot (a barrier after its copy has
+// been passed) and the second is in flight or landed.
+template <class C, class Hook>
+__device__ __attribute__((always_inline)) inline void cell_frame(
+    const unsigned short* im, const unsigned short* it, int plane, CellTab<typename C::F>& T,
+    f32x4 (&acc)[C::G], Hook& hook) {
+  cell_class<C, 0>(im, it, plane, T, acc, hook);
+  cell_class<C, 1>(im + C::PITCH, it + C::PITCH, plane, T, acc, hook);
+  cell_class<C, 2>(im + 2 * C::PITCH, it + 2 * C::PITCH, plane, T, acc, hook);
+  cell_class<C, 3>(im + 3 * C::PITCH, it + 3 * C::PITCH, plane, T, acc, hook);
+}
+
+}  // namespace em

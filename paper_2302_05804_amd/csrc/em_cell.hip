@@ -1,0 +1,523 @@
+// em_cell.hip -- kernels of one EM iteration on the 4 x 4 cell core of em_cell.h:
+// forward model, weighting and adjoint of Eq. (2) (arXiv:2302.05804, Sec. 2) for
+// sr = 1 and kernels padded to 43 x 43, in the BF16 forms and in FP32.
+#include "em_cell.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace em {
+
+namespace {
+
+// 128 x 128 outputs per workgroup, 8 waves of 8 cell rows x 16 cells; 64 x 128 and
+// 4 cell rows per wave in FP32, whose three image planes take half the LDS more
+template <int PREC, bool BAND>
+using CellOf = CellCfg<CellForm<PREC, BAND>, PREC == EM_FP32 ? 4 : 8, 4, 2>;
+
+// Position of this lane: cell row pr of its outputs, its cell's first column.
+struct CellLane {
+  int row0, col;   // image row of group 0's outputs of this lane, first of 4 columns
+};
+
+template <class C>
+__device__ inline CellLane cell_lane(int k0, int l0) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  return {k0 + (w / C::WC) * 4 * C::G + (lane >> 4), l0 + (w % C::WC) * 64 + 4 * (lane & 15)};
+}
+
+// Offsets (halves) of this lane's window in a staged plane: main and tail chunk.
+template <class C>
+__device__ inline int cell_main_off() {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  return (w / C::WC) * 4 * C::G * C::PITCH + (w % C::WC) * 64 + 4 * (lane & 15) + 8 * (lane >> 4);
+}
+template <class C>
+__device__ inline int cell_tail_off() {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gq = lane >> 4;
+  return (w / C::WC) * 4 * C::G * C::PITCH + (w % C::WC) * 64 + 4 * (lane & 15) +
+         (gq >> 1) * 4 * C::PITCH + 32 + 8 * (gq & 1);
+}
+
+__device__ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// Four consecutive values of row `row` from column `col` (clamped into the
+// image; a clamped value is never used).
+__device__ inline void load4(const float* __restrict__ p, int row, int col, int H, int W, bool vec,
+                             float (&v)[4]) {
+  const int64_t base = (int64_t)min(row, H - 1) * W;
+  if (vec) {
+    const float4 q = *reinterpret_cast<const float4*>(p + base + col);
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[base + min(col + i, W - 1)];
+  }
+}
+__device__ inline void store4(float* __restrict__ p, int row, int col, int W, bool vec,
+                              const float (&v)[4]) {
+  float* q = p + (int64_t)row * W + col;
+  if (vec) {
+    *reinterpret_cast<float4*>(q) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (col + i < W) q[i] = v[i];
+  }
+}
+
+// The image tile of a workgroup on its way into the LDS planes: raw pixels in
+// registers, then split and stored.  A wave takes the rows w, w + NW, ... of the
+// tile, its first COLS / 4 lanes four columns each, so that the row address is
+// scalar and the column arithmetic is done once.  Loads read 16 bytes from
+// addresses clamped into the image (all are in flight together); values outside
+// it become 0 when stored.
+template <class C>
+struct CellTile {
+  using F = typename C::F;
+  struct __attribute__((packed, aligned(4))) Quad { float v[4]; };
+  static constexpr int NR = (C::ROWS + C::NW - 1) / C::NW;   // rows per wave
+  static constexpr int PLANE = C::ROWS * C::PITCH;
+  static_assert(C::COLS % 4 == 0 && C::COLS <= 256, "four columns per lane");
+  int H, W, r0, w;
+  int gx;       // image column of this lane's first value
+  bool inner;   // every column of the tile is inside the image (uniform)
+  f32x4 v[NR];
+  __device__ CellTile(int H_, int W_, int k0, int l0, int w_)
+      : H(H_), W(W_), r0(k0 - CELL_OFF), w(w_),
+        gx(l0 - CELL_OFF + 4 * min((int)(threadIdx.x & 63), C::COLS / 4 - 1)),
+        inner(l0 - CELL_OFF >= 0 && l0 - CELL_OFF + C::COLS <= W_) {}
+  // first column read: the four columns from gx, moved inside an image of at least
+  // four columns
+  __device__ int first(int g) const { return min(max(g, 0), max(W - 4, 0)); }
+  __device__ void load(const float* __restrict__ src) {
+    int g = gx;
+    __asm__ volatile("" : "+v"(g));   // keep the address arithmetic here
+    const int c = first(g);
+    if (W >= 4) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const int gy = min(max(r0 + w + C::NW * i, 0), H - 1);
+        const Quad q = *reinterpret_cast<const Quad*>(src + (int64_t)gy * W + c);
+        v[i] = f32x4{q.v[0], q.v[1], q.v[2], q.v[3]};
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const float* rp = src + (int64_t)min(max(r0 + w + C::NW * i, 0), H - 1) * W;
+        v[i] = f32x4{rp[0], rp[min(1, W - 1)], rp[min(2, W - 1)], 0.f};
+      }
+    }
+  }
+  __device__ void store(unsigned short* sh) {
+    int g = gx;
+    __asm__ volatile("" : "+v"(g));
+    if (!inner) {
+      // move each value to its column, 0 outside the image
+      const int d = g - first(g);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const f32x4 o = v[i];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int at = x + d;
+          const float val = at <= 0 ? o[0] : at == 1 ? o[1] : at == 2 ? o[2] : o[3];
+          v[i][x] = (g + x >= 0 && g + x < W) ? val : 0.f;
+        }
+      }
+    }
+    if ((int)(threadIdx.x & 63) >= C::COLS / 4) return;
+    unsigned short* dst = sh + w * C::PITCH + 4 * (threadIdx.x & 63);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int row = w + C::NW * i, gy = r0 + row;
+      if ((i + 1) * C::NW > C::ROWS && row >= C::ROWS) break;
+      const bool iny = gy >= 0 && gy < H;
+      uint32_t a[F::NB], b[F::NB];
+      cell_split2<F::PREC>(iny ? f32x2{v[i][0], v[i][1]} : f32x2{0.f, 0.f}, a);
+      cell_split2<F::PREC>(iny ? f32x2{v[i][2], v[i][3]} : f32x2{0.f, 0.f}, b);
+#pragma unroll
+      for (int p = 0; p < F::NA; ++p)
+        *reinterpret_cast<uint2*>(dst + p * PLANE + C::NW * i * C::PITCH) = make_uint2(a[p], b[p]);
+    }
+  }
+};
+
+// The forward's weights of this lane's outputs, loaded while the last class of
+// the frame runs, so that the epilogue does not wait for HBM.
+template <class C>
+struct CellWeights {
+  const float* ut;   // frame base, nullptr: nothing to load
+  int H, W;
+  CellLane p;
+  bool vec;
+  float4 uu[C::G];
+  __device__ void wait(int) const { cell_wait<0>(); }
+  __device__ void after(int b) {
+    if (b == C::F::UPF - 2 && ut != nullptr && vec) {
+#pragma unroll
+      for (int g = 0; g < C::G; ++g)
+        uu[g] = *reinterpret_cast<const float4*>(ut + (int64_t)min(p.row0 + 4 * g, H - 1) * W + p.col);
+    }
+  }
+};
+
+// Forward: r_t = u_t (f_t * x) for the frames of this group, or m when u is NULL
+// (FP64 partials of u (y - m)^2 when asked); STUDENT: the E-step weights, u w m
+// and u w y.  The x tile is staged once.
+template <class C, bool STUDENT>
+__device__ inline void cell_fwd_body(const MfmaLaunch& a, const int tile, const int group) {
+  using F = typename C::F;
+  using frag = typename C::frag;
+  constexpr int PLANE = C::ROWS * C::PITCH;
+  __shared__ __align__(16) unsigned short sh[F::NA * PLANE];
+  __shared__ __align__(16) frag slot0[F::NFU * 64];
+  __shared__ __align__(16) frag slot1[F::NFU * 64];
+  __shared__ double red[C::NW];
+  const int tiles_x = (a.W + C::TW - 1) / C::TW;
+  const int k0 = (tile / tiles_x) * C::TH, l0 = (tile % tiles_x) * C::TW;
+  const int t0 = group * a.fpg;
+  const int t1 = min(a.n, t0 + a.fpg);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  CellTab<F> T{reinterpret_cast<const frag*>(a.tab) + (int64_t)t0 * F::FRAME, 0,
+               (t1 - t0) * F::UPF, w, {slot0, slot1}};
+  cell_issue_unit<C>(T.tab, 0, w, slot0);
+  cell_issue_unit<C>(T.tab, 1, w, slot1);
+  {
+    CellTile<C> tl(a.H, a.W, k0, l0, w);
+    tl.load(a.in);
+    tl.store(sh);
+  }
+  cell_wait<0>();
+  __syncthreads();
+
+  const int64_t N = (int64_t)a.H * a.W;
+  const CellLane lane_pos = cell_lane<C>(k0, l0);
+  const unsigned short* im = sh + cell_main_off<C>();
+  const unsigned short* it = sh + cell_tail_off<C>();
+  const bool ll = a.part != nullptr;
+  const bool al = (a.W & 3) == 0 && aligned16(a.u) && (a.out == nullptr || aligned16(a.out)) &&
+                  (!(STUDENT || ll) || aligned16(a.y)) &&
+                  (!STUDENT || aligned16(a.out_y));
+  const bool vec = al && lane_pos.col + 3 < a.W;
+  double llp = 0.0;
+  for (int t = t0; t < t1; ++t) {
+    // the staged tile does not change between frames: keep its reads inside the
+    // loop, and the epilogue's address arithmetic (held in registers over the
+    // products, it would spill)
+    CellLane p = lane_pos;
+    __asm__ volatile("" : "+v"(p.row0), "+v"(p.col)::"memory");
+    f32x4 acc[C::G];
+#pragma unroll
+    for (int g = 0; g < C::G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float* ut = a.u ? a.u + (int64_t)t * N : nullptr;
+    CellWeights<C> hook{ut, a.H, a.W, p, vec, {}};
+    cell_frame<C>(im, it, PLANE, T, acc, hook);
+    const float* yt = (STUDENT || (ll && ut)) ? a.y + (int64_t)t * N : nullptr;
+    float* ot = a.out ? a.out + (int64_t)t * N : nullptr;
+#pragma unroll
+    for (int g = 0; g < C::G; ++g) {
+      const int k = p.row0 + 4 * g;
+      const float m[4] = {acc[g][0], acc[g][1], acc[g][2], acc[g][3]};
+      float u[4] = {1.f, 1.f, 1.f, 1.f}, y[4] = {0.f, 0.f, 0.f, 0.f};
+      if (ut) {
+        if (vec) {
+          u[0] = hook.uu[g].x; u[1] = hook.uu[g].y; u[2] = hook.uu[g].z; u[3] = hook.uu[g].w;
+        } else {
+          load4(ut, k, p.col, a.H, a.W, false, u);
+        }
+      }
+      if (yt) load4(yt, k, p.col, a.H, a.W, vec, y);
+      if (k >= a.H || p.col >= a.W) continue;
+      float r[4], ry[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool in = p.col + i < a.W;
+        if constexpr (STUDENT) {
+          r[i] = 0.f;
+          ry[i] = 0.f;
+          if (u[i] > 0.f) {
+            const float d = y[i] - m[i];
+            const float w = (a.nu + 1.f) / (a.nu + u[i] * d * d);
+            r[i] = (u[i] * w) * m[i];
+            ry[i] = (u[i] * w) * y[i];
+            if (ll && in) {
+              const double dd = (double)y[i] - (double)m[i];
+              llp += ((double)a.nu + 1.0) * log1p((double)u[i] * dd * dd / (double)a.nu) - a.lcst;
+            }
+          }
+        } else {
+          r[i] = ut ? u[i] * m[i] : m[i];
+          if (yt && in && u[i] > 0.f) {
+            const double d = (double)y[i] - (double)m[i];
+            llp += (double)u[i] * d * d;
+          }
+        }
+      }
+      if (ot) store4(ot, k, p.col, a.W, vec, r);
+      if constexpr (STUDENT) store4(a.out_y + (int64_t)t * N, k, p.col, a.W, vec, ry);
+    }
+  }
+  cell_wait<0>();   // the copies issued past the last unit
+  if (a.part != nullptr) {
+    const double s = block_sum<C::NT>(llp, red);
+    if (threadIdx.x == 0) a.part[(int64_t)group * a.ntiles + tile] = s;
+  }
+}
+
+// Epilogue of the adjoint: Dn = acc; the fused update of Eq. (2) with its FP64
+// change partials, or a store into the partial plane.
+template <class C>
+__device__ inline void cell_adj_epilogue(const MfmaLaunch& a, const f32x4 (&acc)[C::G],
+                                         const CellLane& p, int tile, int group, double* red) {
+  const int64_t N = (int64_t)a.H * a.W;
+  float* plane = a.fused ? nullptr : a.plane + (int64_t)group * N;
+  const bool al = (a.W & 3) == 0 && (a.fused ? aligned16(a.x) && aligned16(a.B) : aligned16(plane));
+  const bool vec = al && p.col + 3 < a.W;
+  double dsq = 0.0, xsq = 0.0;
+  if (!a.fused) {
+#pragma unroll
+    for (int g = 0; g < C::G; ++g) {
+      const int k = p.row0 + 4 * g;
+      const float v[4] = {acc[g][0], acc[g][1], acc[g][2], acc[g][3]};
+      if (k < a.H && p.col < a.W) store4(plane, k, p.col, a.W, vec, v);
+    }
+    return;
+  }
+  float xo[C::G][4], bv[C::G][4];
+#pragma unroll
+  for (int g = 0; g < C::G; ++g) {
+    load4(a.x, p.row0 + 4 * g, p.col, a.H, a.W, vec, xo[g]);
+    load4(a.B, p.row0 + 4 * g, p.col, a.H, a.W, vec, bv[g]);
+  }
+#pragma unroll
+  for (int g = 0; g < C::G; ++g) {
+    const int k = p.row0 + 4 * g;
+    if (k >= a.H || p.col >= a.W) continue;
+    float xn[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      xn[i] = em_update_value(xo[g][i], bv[g][i], acc[g][i]);
+      if (p.col + i < a.W) {
+        const double d = (double)xn[i] - (double)xo[g][i];
+        dsq += d * d;
+        xsq += (double)xo[g][i] * (double)xo[g][i];
+      }
+    }
+    store4(a.x, k, p.col, a.W, vec, xn);
+  }
+  if (a.part != nullptr) {
+    const double s1 = block_sum<C::NT>(dsq, red);
+    __syncthreads();
+    const double s2 = block_sum<C::NT>(xsq, red + C::NW);
+    if (threadIdx.x == 0) {
+      a.part[2 * tile] = s1;
+      a.part[2 * tile + 1] = s2;
+    }
+  }
+}
+
+// The next frame's r tile, loaded into registers while the last rows of the
+// current frame's last class run (loaded a boundary earlier, it spilled: 2.72
+// instead of 2.48 ms on 33 x 2048^2 in FP32).
+template <class C>
+struct CellTileHook {
+  CellTile<C> tl;
+  const float* next;
+  __device__ void wait(int) const { cell_wait<0>(); }
+  __device__ void after(int b) {
+    if (b == C::F::UPF - 1) tl.load(next);
+  }
+};
+
+// Adjoint: sum over the frames of this group of F_t^T r_t; the r_t tile is staged
+// per frame.
+template <class C>
+__device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const int group) {
+  using F = typename C::F;
+  using frag = typename C::frag;
+  using Hook = CellTileHook<C>;
+  constexpr int PLANE = C::ROWS * C::PITCH;
+  __shared__ __align__(16) unsigned short sh[F::NA * PLANE];
+  __shared__ __align__(16) frag slot0[F::NFU * 64];
+  __shared__ __align__(16) frag slot1[F::NFU * 64];
+  __shared__ double red[2 * C::NW];
+  const int tiles_x = (a.W + C::TW - 1) / C::TW;
+  const int k0 = (tile / tiles_x) * C::TH, l0 = (tile % tiles_x) * C::TW;
+  const int64_t N = (int64_t)a.H * a.W;
+  const int t0 = group * a.fpg;
+  const int t1 = min(a.n, t0 + a.fpg);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  CellTab<F> T{reinterpret_cast<const frag*>(a.tab) + (int64_t)t0 * F::FRAME, 0,
+               (t1 - t0) * F::UPF, w, {slot0, slot1}};
+  cell_issue_unit<C>(T.tab, 0, w, slot0);
+  cell_issue_unit<C>(T.tab, 1, w, slot1);
+  const CellLane p = cell_lane<C>(k0, l0);
+  const unsigned short* im = sh + cell_main_off<C>();
+  const unsigned short* it = sh + cell_tail_off<C>();
+  f32x4 acc[C::G];
+#pragma unroll
+  for (int g = 0; g < C::G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Hook hook{CellTile<C>(a.H, a.W, k0, l0, w), a.in + (int64_t)t0 * N};
+  hook.tl.load(hook.next);
+  for (int t = t0; t < t1; ++t) {
+    hook.tl.store(sh);
+    cell_wait<0>();
+    __syncthreads();
+    hook.next = a.in + (int64_t)min(t + 1, t1 - 1) * N;
+    // each frame is summed by itself and then added to the total
+    f32x4 accf[C::G];
+#pragma unroll
+    for (int g = 0; g < C::G; ++g) accf[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    cell_frame<C>(im, it, PLANE, T, accf, hook);
+#pragma unroll
+    for (int g = 0; g < C::G; ++g) acc[g] += accf[g];
+    __syncthreads();   // every wave is done with the tile
+  }
+  cell_wait<0>();   // the copies issued past the last unit
+  cell_adj_epilogue<C>(a, acc, p, tile, group, red);
+}
+
+// One job per launch, grid (tiles, frame groups), or the (job, tile, group) items
+// of several jobs strided over by the workgroups.
+enum { K_FWD = 0, K_FWD_T = 1, K_ADJ = 2 };
+
+template <class C, int KIND>
+__device__ inline void cell_body(const MfmaLaunch& a, int tile, int group) {
+  if constexpr (KIND == K_ADJ) cell_adj_body<C>(a, tile, group);
+  else cell_fwd_body<C, KIND == K_FWD_T>(a, tile, group);
+}
+
+template <class C, int KIND>
+__global__ __launch_bounds__(C::NT) void cell_kernel(MfmaLaunch a) {
+  cell_body<C, KIND>(a, blockIdx.x, blockIdx.y);
+}
+
+template <class C, int KIND>
+__global__ __launch_bounds__(C::NT) void cell_batched(const MfmaLaunch* __restrict__ descs,
+                                                      const int4* __restrict__ items, int n_items) {
+  for (int i = blockIdx.x; i < n_items; i += gridDim.x) {
+    const int4 w = items[i];
+    const MfmaLaunch d = descs[w.x];
+    cell_body<C, KIND>(d, w.y, w.z);
+    __syncthreads();
+  }
+}
+
+// Table of one frame (blockIdx.x), one unit per blockIdx.y: lane (m, gq) of a
+// fragment holds T[m][window row, column 8 gq + e] of its part (see em_cell.h);
+// dir 0: g = f flipped (forward), dir 1: g = f; f zero-padded from K to 43.
+template <class F>
+__global__ __launch_bounds__(256) void cell_table_kernel(const float* psf, int K, int dir,
+                                                         unsigned short* tab) {
+  const int t = blockIdx.x, unit = blockIdx.y, E = unit / F::NU, u = unit % F::NU;
+  const int off = (CELL_K - K) / 2;
+  const float* f = psf + (int64_t)t * K * K;
+  for (int i = threadIdx.x; i < F::NFU * 64; i += 256) {
+    const int lane = i & 63, m = lane & 15, gq = lane >> 4;
+    int part = -1, j = 0;
+    bool tail = false;
+    for (int p = 0; p < F::NB; ++p)
+      for (int jj = u * F::JU; jj < (u + 1) * F::JU; ++jj) {
+        if (F::has_main(p, jj) && F::slot(p, jj, false) == i >> 6) { part = p; j = jj; tail = false; }
+        if (F::has_tail(p, jj) && F::slot(p, jj, true) == i >> 6) { part = p; j = jj; tail = true; }
+      }
+    unsigned short* dst = tab + (((int64_t)t * F::UPF + unit) * F::NFU * 64 + i) * 8;
+    for (int e = 0; e < 8; ++e) {
+      // window row and column of this K position
+      const int d = 4 * (j + (tail ? gq >> 1 : 0)) + E;
+      const int k = tail ? 32 + 8 * (gq & 1) + e : 8 * gq + e;
+      const int ta = d - 1 - (m >> 2), tb = k - 1 - (m & 3);
+      float gv = 0.f;
+      if (part >= 0 && ta >= 0 && ta < CELL_K && tb >= 0 && tb < CELL_K &&
+          (part == 0 || !F::BAND || (ta >= 11 && ta <= 31))) {
+        const int fa = (dir == 0 ? CELL_K - 1 - ta : ta) - off;
+        const int fb = (dir == 0 ? CELL_K - 1 - tb : tb) - off;
+        if (fa >= 0 && fa < K && fb >= 0 && fb < K) gv = f[fa * K + fb];
+      }
+      uint32_t q[F::NB];
+      cell_split2<F::PREC>(f32x2{gv, 0.f}, q);
+      uint32_t out = 0;
+      for (int x = 0; x < F::NB; ++x) out = x == part ? q[x] : out;
+      dst[e] = (unsigned short)out;
+    }
+  }
+}
+
+template <int PREC, bool BAND>
+hipError_t launch_one(int kind, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
+  using C = CellOf<PREC, BAND>;
+  const dim3 block(C::NT);
+  if (kind == K_FWD) hipLaunchKernelGGL((cell_kernel<C, K_FWD>), grid, block, 0, s, a);
+  else if (kind == K_FWD_T) hipLaunchKernelGGL((cell_kernel<C, K_FWD_T>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((cell_kernel<C, K_ADJ>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+template <int PREC, bool BAND>
+hipError_t launch_many(int kind, int grid, const MfmaLaunch* d, const int4* it, int n, hipStream_t s) {
+  using C = CellOf<PREC, BAND>;
+  const dim3 block(C::NT);
+  if (kind == K_FWD) hipLaunchKernelGGL((cell_batched<C, K_FWD>), dim3(grid), block, 0, s, d, it, n);
+  else if (kind == K_FWD_T) hipLaunchKernelGGL((cell_batched<C, K_FWD_T>), dim3(grid), block, 0, s, d, it, n);
+  else hipLaunchKernelGGL((cell_batched<C, K_ADJ>), dim3(grid), block, 0, s, d, it, n);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int cell_tile_h(int precision) {
+  return precision == EM_FP32 ? CellOf<EM_FP32, false>::TH : CellOf<EM_BF16, false>::TH;
+}
+static_assert(CellOf<EM_FP32, false>::TW == CELL_TILE_W && CellOf<EM_BF16, false>::TW == CELL_TILE_W, "tile");
+
+size_t cell_table_bytes(int precision, int n) {
+  const int64_t lanes = precision == EM_FP32         ? CellForm<EM_FP32, false>::FRAME
+                        : precision == EM_BF16_SPLIT ? std::max(CellForm<EM_BF16_SPLIT, false>::FRAME,
+                                                                CellForm<EM_BF16_SPLIT, true>::FRAME)
+                                                     : CellForm<EM_BF16, false>::FRAME;
+  return (size_t)n * lanes * 16;
+}
+
+// The BF16 split form takes its band for jobs whose PSFs passed the band check,
+// and not in serving.
+hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
+  if (a.r16 != nullptr) return hipErrorInvalidValue;
+  const int kind = dir == 1 ? K_ADJ : a.out_y ? K_FWD_T : K_FWD;
+  switch (precision) {
+    case EM_FP32: return launch_one<EM_FP32, false>(kind, grid, a, s);
+    case EM_BF16_SPLIT:
+      return a.lo_band ? launch_one<EM_BF16_SPLIT, true>(kind, grid, a, s)
+                       : launch_one<EM_BF16_SPLIT, false>(kind, grid, a, s);
+    case EM_BF16: return launch_one<EM_BF16, false>(kind, grid, a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, const int4* items,
+                               int n_items, int grid, hipStream_t s, bool robust) {
+  const int kind = dir == 1 ? K_ADJ : robust ? K_FWD_T : K_FWD;
+  switch (precision) {
+    case EM_BF16_SPLIT: return launch_many<EM_BF16_SPLIT, false>(kind, grid, descs, items, n_items, s);
+    case EM_BF16: return launch_many<EM_BF16, false>(kind, grid, descs, items, n_items, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
+                              bool lo_band, hipStream_t s) {
+  for (int dir = 0; dir < 2; ++dir) {
+    unsigned short* t = static_cast<unsigned short*>(dir == 0 ? tab_fwd : tab_adj);
+    auto go = [&](auto form) {
+      using F = decltype(form);
+      hipLaunchKernelGGL(cell_table_kernel<F>, dim3(g.n, F::UPF), dim3(256), 0, s, psf, g.K, dir, t);
+    };
+    if (g.precision == EM_FP32) go(CellForm<EM_FP32, false>{});
+    else if (g.precision == EM_BF16) go(CellForm<EM_BF16, false>{});
+    else if (lo_band) go(CellForm<EM_BF16_SPLIT, true>{});
+    else go(CellForm<EM_BF16_SPLIT, false>{});
+  }
+  return hipGetLastError();
+}
+
+}  // namespace em

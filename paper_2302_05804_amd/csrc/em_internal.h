@@ -48,6 +48,10 @@ struct Geometry {
   int64_t Nf, Nl;
   int precision, weight_mode;
   float nu;   // Student-t degrees of freedom (EM_W_STUDENT_T)
+  // FP32 form on the matrix cores (em_cell.hip: three bf16 parts of each operand):
+  // set by make_geometry where that path is the faster one, cleared where its
+  // tables do not fit (serving arenas, the static scratch)
+  int mc32;
 };
 
 // Launch shape chosen for a geometry (a pure function of the geometry, so the
@@ -80,7 +84,12 @@ struct Layout {
 
 // true when the convolutions of geometry g run on the matrix cores
 inline bool uses_mfma(const Geometry& g) {
-  return g.precision == EM_BF16_SPLIT || g.precision == EM_FP16_SPLIT || g.precision == EM_BF16;
+  return g.precision == EM_BF16_SPLIT || g.precision == EM_FP16_SPLIT || g.precision == EM_BF16 ||
+         g.mc32 != 0;
+}
+// sr = 1 jobs on the 4 x 4 cell kernels (em_cell.hip)
+inline bool uses_cell(const Geometry& g) {
+  return g.sr == 1 && g.KT == KT_LARGE && uses_mfma(g) && g.precision != EM_FP16_SPLIT;
 }
 
 bool make_geometry(const void* problem, Geometry* g, const char** why);
@@ -199,6 +208,15 @@ hipError_t launch_r16_scale_batched(const R16Job* jobs, int n_jobs, hipStream_t 
 hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int groups,
                        const MfmaLaunch& a, hipStream_t s);
 int mfma_table_rows(int KT);
+// the 4 x 4 cell kernels (em_cell.hip); cell_tile_h x 128 outputs per workgroup
+int cell_tile_h(int precision);
+constexpr int CELL_TILE_W = 128;
+size_t cell_table_bytes(int precision, int n);
+hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s);
+hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, const int4* items,
+                               int n_items, int grid, hipStream_t s, bool robust);
+hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
+                              bool lo_band, hipStream_t s);
 // sr = 2 matrix-core kernels (em_mfma2.hip); K <= 43 padded to 43
 hipError_t launch_mfma2(const Geometry& g, int dir, int variant, int tiles, int groups,
                         const MfmaLaunch& a, hipStream_t s);
@@ -232,8 +250,8 @@ hipError_t launch_adjoint_batched(int sr, int KT, const AdjLaunch* descs, const 
                                   int n_items, int grid, hipStream_t s);
 int mfma_variants();
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
-                              hipStream_t s);
-int mfma_tile_h();
+                              hipStream_t s, bool lo_band = false);
+int mfma_tile_h(const Geometry& g);   // outputs of a workgroup, sr = 1
 int mfma_tile_w();
 size_t mfma_table_bytes(const Geometry& g, int dir);
 

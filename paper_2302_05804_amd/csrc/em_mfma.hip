@@ -13,8 +13,8 @@
 // p-values of a column of U_a are non-zero.
 //
 // Precision (template argument PREC, encodings in em_mfma_common.h): bf16 hi +
-// lo split of both operands with three products (EM_BF16_SPLIT), plain bf16
-// (EM_BF16), or a binary16 image operand with a per-tile power-of-two scale
+// lo split of both operands with three products (EM_BF16_SPLIT) and plain bf16
+// (EM_BF16), both for kernels padded to 15 (43: em_cell.hip), or a binary16 image operand with a per-tile power-of-two scale
 // times a binary16 hi + lo PSF with a per-frame scale, two products
 // (EM_FP16_SPLIT).  Accumulation is FP32 in the matrix core throughout.
 //
@@ -42,7 +42,7 @@ constexpr int MF_TILE = 128;   // every sr = 1 variant covers 128 x 128 outputs
 
 // Tile configuration: each wave owns BR x BC blocks of 16 x 16 outputs, the
 // workgroup WR x WC waves.
-template <int KT_, int PREC_, int BR_, int BC_, int WR_, int WC_, int PFA_, int PFT_, int LB_ = -1>
+template <int KT_, int PREC_, int BR_, int BC_, int WR_, int WC_, int PFA_, int PFT_>
 struct MfCfg {
   using P = Prec<PREC_>;
   using frag = typename P::frag;
@@ -63,15 +63,12 @@ struct MfCfg {
   static constexpr int NTF = MMAX * 2 * NB;     // Toeplitz fragments of one class
   static constexpr int RFULL = KT - 16 * (MMAX - 1);     // classes with MMAX members
   static constexpr int RLAST = (MMAX == 1) ? KT : 16;    // number of classes
-  // K = 43, FP16 split (always) or BF16 split (LB_ = 1, for jobs whose PSFs keep
-  // at most 1/16 of their mass outside the band): the lo parts enter only on the
-  // 21 kernel rows within 10 of the centre (rows 11..31: member 1 of the
-  // three-member classes r <= 10, both members of the classes r >= 11), where a
-  // PSF keeps its core; elsewhere each tap is the product of the hi parts alone
-  // (the PSF's relative error 2^-11 in binary16; in bf16 2^-9 for the PSF and
-  // for the image operand each).  Bit m of lo_mask(NM): member m takes lo.
-  static constexpr bool BAND =
-      KT_ == 43 && (LB_ < 0 ? PREC_ == EM_FP16_SPLIT : (LB_ == 1 && PREC_ != EM_BF16));
+  // K = 43 (FP16 split): the lo parts enter only on the 21 kernel rows within 10
+  // of the centre (rows 11..31: member 1 of the three-member classes r <= 10,
+  // both members of the classes r >= 11), where a PSF keeps its core; elsewhere
+  // each tap is the product of the hi parts alone (the PSF's relative error
+  // 2^-11 in binary16).  Bit m of lo_mask(NM): member m takes lo.
+  static constexpr bool BAND = KT_ == 43 && PREC_ == EM_FP16_SPLIT;
   static constexpr int lo_mask(int nm) { return !BAND ? 7 : (nm == 3 ? 2 : 3); }
 };
 
@@ -125,8 +122,8 @@ __device__ inline void mfma_class(int r, const unsigned short (*sh)[C::ROWS * C:
   constexpr int LOM = C::lo_mask(NM);
   typename C::frag A[C::PFA ? 2 : 1][C::BC + 2][C::NA];
   if (C::PFA) load_A<C>(A[0], sh, row_base + r + i, col_base);
-  // two-plane forms: the wave issuing products runs at raised priority (3% off
-  // the BF16 split adjoint on c3; no gain for the binary16 form)
+  // two-plane forms: the wave issuing products runs at raised priority (no gain
+  // for the binary16 form)
   constexpr bool PRIO = C::NA == 2;
   if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -861,8 +858,9 @@ __global__ __launch_bounds__(256) void mfma_table_kernel(const float* psf, int n
 int mfma_table_rows(int KT) { return 16 * ((KT + 15) / 16); }
 
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
-                              hipStream_t s) {
+                              hipStream_t s, bool lo_band) {
   if (g.sr == 2) return launch_mfma2_tables(g, psf, tab_fwd, tab_adj, s);
+  if (uses_cell(g)) return launch_cell_tables(g, psf, tab_fwd, tab_adj, lo_band, s);
   const int KTP = mfma_table_rows(g.KT);
   dim3 grid(g.n, KTP);
   for (int dir = 0; dir < 2; ++dir) {
@@ -877,11 +875,12 @@ hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd
   return hipGetLastError();
 }
 
-int mfma_tile_h() { return MF_TILE; }
+int mfma_tile_h(const Geometry& g) { return uses_cell(g) ? cell_tile_h(g.precision) : MF_TILE; }
 int mfma_tile_w() { return MF_TILE; }
 
 size_t mfma_table_bytes(const Geometry& g, int dir) {
   if (g.sr == 2) return dir == 0 && uses_m2n(g) ? mfma2n_table_bytes(g.n) : mfma2_table_bytes(g.n, dir);
+  if (g.mc32) return cell_table_bytes(g.precision, g.n);
   // fragments, then one scale exponent per frame
   return (size_t)g.n * mfma_table_rows(g.KT) * 4 * 64 * 8 * sizeof(uint16_t) +
          (size_t)g.n * sizeof(int);
@@ -919,28 +918,6 @@ hipError_t launch_dir(int dir, int variant, dim3 grid, const MfmaLaunch& a, hipS
     }
   } else {
     if (a.r16 != nullptr) return hipErrorInvalidValue;
-  }
-  if constexpr (PREC == EM_BF16_SPLIT && KT == 43) {
-    // the BF16 split iteration of a job whose PSFs pass the band check
-    if (a.lo_band) {
-      using B0 = MfCfg<KT, PREC, 4, 4, 2, 2, 1, PFT, 1>;
-      using B1 = MfCfg<KT, PREC, 4, 2, 2, 4, 0, PFT, 1>;
-      using B2 = MfCfg<KT, PREC, 2, 4, 4, 2, 0, PFT, 1>;
-      if (dir == 0 && a.out_y != nullptr) {
-        if (variant == 1) hipLaunchKernelGGL(mfma_fwd_t_kernel<B1>, grid, dim3(B1::NT), 0, s, a);
-        else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_t_kernel<B2>, grid, dim3(B2::NT), 0, s, a);
-        else hipLaunchKernelGGL(mfma_fwd_t_kernel<B0>, grid, dim3(B0::NT), 0, s, a);
-      } else if (dir == 0) {
-        if (variant == 1) hipLaunchKernelGGL(mfma_fwd_kernel<B1>, grid, dim3(B1::NT), 0, s, a);
-        else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_kernel<B2>, grid, dim3(B2::NT), 0, s, a);
-        else hipLaunchKernelGGL(mfma_fwd_kernel<B0>, grid, dim3(B0::NT), 0, s, a);
-      } else {
-        if (variant == 1) hipLaunchKernelGGL(mfma_adj_kernel<B1>, grid, dim3(B1::NT), 0, s, a);
-        else if (variant == 2) hipLaunchKernelGGL(mfma_adj_kernel<B2>, grid, dim3(B2::NT), 0, s, a);
-        else hipLaunchKernelGGL(mfma_adj_kernel<B0>, grid, dim3(B0::NT), 0, s, a);
-      }
-      return hipGetLastError();
-    }
   }
   if (dir == 0 && a.out_y != nullptr) {
     if (variant == 1) hipLaunchKernelGGL(mfma_fwd_t_kernel<C1>, grid, dim3(C1::NT), 0, s, a);
@@ -1018,7 +995,11 @@ hipError_t launch_mfma_batched(int KT, int precision, int dir, int variant, cons
     default:                                                                                 \
       return hipErrorInvalidValue;                                                           \
   }
-  if (KT == KT_LARGE) { EM_MF_DISPATCH(KT_LARGE) }
+  if (KT == KT_LARGE && precision != EM_FP16_SPLIT)
+    return r16 ? hipErrorInvalidValue
+               : launch_cell_batched(precision, dir, descs, items, n_items, grid, s, robust);
+  if (KT == KT_LARGE && precision == EM_FP16_SPLIT)
+    return launch_dir_batched<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, descs, items, n_items, s, robust, r16);
   EM_MF_DISPATCH(KT_SMALL)
 #undef EM_MF_DISPATCH
 }
@@ -1032,7 +1013,7 @@ bool mfma_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaL
     return false;
   if (g.sr == 2) return mfma2_desc_ok(g, dir, tiles, groups, a);
   return a.H == g.Hl && a.W == g.Wl &&
-         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, MF_TILE, MF_TILE);
+         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g), MF_TILE);
 }
 
 int r16_pitch(const Geometry& g) {
@@ -1240,7 +1221,10 @@ hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int g
     case EM_BF16: return launch_dir<KTV, EM_BF16>(dir, variant, grid, a, s);             \
     default: return hipErrorInvalidValue;                                    \
   }
-  if (g.KT == KT_LARGE) { EM_MF_DISPATCH(KT_LARGE) }
+  if (uses_cell(g)) return launch_cell(g.precision, dir, grid, a, s);
+  if (g.KT == KT_LARGE)
+    return g.precision == EM_FP16_SPLIT ? launch_dir<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, a, s)
+                                        : hipErrorInvalidValue;
   EM_MF_DISPATCH(KT_SMALL)
 #undef EM_MF_DISPATCH
 }

@@ -1,0 +1,80 @@
+"""The 4 x 4 cell kernels (sr = 1, kernels padded to 43 x 43) at the edges of
+their tiles, cells and 16-byte accesses, against the FP64 oracle.
+
+FP32 runs on them from frames of 128 x 128 pixels on, as three bf16 parts per
+operand: the split is exact, each product left out is below 2^-24 of the whole
+one and at most three are, and a sum passes through fewer than 40 roundings of
+2^-24, so every value is within (3 + 40) 2^-24 of the sum of the absolute
+products.  BF16 split: 1e-4 of it, the bar of that form's operators.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2302_05804_amd import synth
+from tests.gpu_common import gpu_run, log, rel_l2, to_dev
+
+pytestmark = pytest.mark.gpu
+
+FP32_BOUND = 43 * 2.0 ** -24
+BF16_BOUND = 1e-4
+
+
+def _em():
+    from paper_2302_05804_amd import em
+    return em
+
+
+@pytest.mark.parametrize("hf,wf", [
+    (128, 128),      # one BF16 tile, two FP32 tiles
+    (129, 257),      # one row and one column into the next tiles
+    (191, 130),      # odd height, width 2 mod 4
+    (65, 515),       # width 3 mod 4
+    (16385, 1), (8193, 2), (5462, 3), (4097, 5),   # narrower than one 16-byte access, or just wider
+])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_operators_at_tile_and_access_edges(prec, hf, wf):
+    em = _em()
+    code, bound = (em.FP32, FP32_BOUND) if prec == "fp32" else (em.BF16_SPLIT, BF16_BOUND)
+    n, K = 2, 43
+    rng = np.random.default_rng(hf * 1000 + wf)
+    psf = rng.uniform(0, 1, (n, K, K)).astype(np.float32)
+    psf /= psf.sum(axis=(1, 2), keepdims=True)
+    # seven decades inside a tile
+    x = np.exp(rng.uniform(np.log(1e-2), np.log(1e5), (hf, wf))).astype(np.float32)
+    r = rng.normal(0, 1, (n, hf, wf)).astype(np.float32)
+    p = em.Problem.make(n, hf, wf, K, precision=code)
+    m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy().astype(np.float64)
+    s = em.adjoint_op(p, to_dev(psf), to_dev(r)).cpu().numpy().astype(np.float64)
+    for t in range(n):
+        mo, so = oracle.forward(psf[t], x, 1), oracle.adjoint(psf[t], r[t], 1)
+        sa = oracle.adjoint(psf[t], np.abs(r[t]), 1)
+        em_, es = np.abs(m[t] - mo) / mo, np.abs(s[t] - so) / sa
+        log(f"{prec} {hf}x{wf} frame {t}: forward {em_.max():.2e}, adjoint {es.max():.2e} of the absolute sums")
+        assert em_.max() <= bound and es.max() <= bound
+
+
+@pytest.mark.parametrize("n", [1, 2, 5])
+def test_fp32_frame_groups(n):
+    """Frame counts that split unevenly over the groups of a small image."""
+    p = synth.make_problem("c2", H=140, W=133, n=n, seed=310 + n)
+    x0 = synth.positive_start(p.latent_shape, 20.0, seed=311)
+    xg, trg = gpu_run(p.y, p.v, p.psf, 1, 4, x0=x0)
+    xo, tro, _ = oracle.run(p.y, p.v, p.psf, x0, 4, trace=True)
+    assert rel_l2(xg, xo) <= 1e-5
+    assert np.abs(trg - tro).max() <= 1e-6 * np.abs(tro).max()
+
+
+def test_fp32_large_and_small_values():
+    """Near the largest binary32 the first part is clamped, not infinite."""
+    em = _em()
+    H, W, K = 130, 130, 43
+    psf = np.zeros((1, K, K), np.float32)
+    psf[0, 21, 21], psf[0, 0, 5] = 0.5, 0.25
+    x = np.full((H, W), np.float32(3.4e38))
+    x[:, 64:] = 1e-30
+    p = em.Problem.make(1, H, W, K)
+    m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy()[0].astype(np.float64)
+    mo = oracle.forward(psf[0], x, 1)
+    assert np.isfinite(m).all()
+    assert np.abs(m / mo - 1).max() <= FP32_BOUND
