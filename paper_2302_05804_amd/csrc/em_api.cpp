@@ -85,6 +85,10 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   // FP32 on the matrix cores: from frames of 128 x 128 pixels on (below, the
   // tables of a frame, 432 KB, would be most of the workspace)
   g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->sr == 1 && g->Nf >= 128 * 128;
+  // small images in the FP16 split form: up to half the compute units' worth of
+  // 128 x 128 tiles over all frames
+  g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 &&
+               cdiv(g->Hf, 128) * cdiv(g->Wf, 128) * g->n <= 128;
   if ((int64_t)g->n * g->Nf > ((int64_t)1 << 40)) { *why = "problem too large"; return false; }
   if (g->Nl >= ((int64_t)1 << 31)) { *why = "latent image of 2^31 pixels or more"; return false; }
   return true;
@@ -120,10 +124,13 @@ Plan make_plan(const Geometry& g) {
     pl.fwd_tiles = (int)(cdiv(g.Wf, mfma2_fwd_tile_w(g.precision)) *
                          cdiv(g.Hf, mfma2_fwd_tile_h(g.precision)));
   else if (mf)
-    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w()) * cdiv(g.Hf, mfma_tile_h(g)));
+    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w(g)) * cdiv(g.Hf, mfma_tile_h(g)));
   else
     pl.fwd_tiles = (int)(cdiv(g.Wf, fwd_tile_w(g)) * cdiv(g.Hf, fwd_tile_h(g)));
-  int fg = (int)std::min<int64_t>(g.n, cdiv(target, pl.fwd_tiles));
+  // 64 x 64 tiles keep the frame groups of 128 x 128 ones (and with them the order
+  // of the frame sum)
+  const int tiles128 = (int)(cdiv(g.Wf, 128) * cdiv(g.Hf, 128));
+  int fg = (int)std::min<int64_t>(g.n, cdiv(target, g.small16 ? tiles128 : pl.fwd_tiles));
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
   if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, g.n));
@@ -134,14 +141,15 @@ Plan make_plan(const Geometry& g) {
     pl.adj_tiles = (int)(cdiv(g.Wl, mfma2_adj_tile_w(g.precision)) *
                          cdiv(g.Hl, mfma2_adj_tile_h(g.precision)));
   else if (mf)
-    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w()) * cdiv(g.Hl, mfma_tile_h(g)));
+    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w(g)) * cdiv(g.Hl, mfma_tile_h(g)));
   else
     pl.adj_tiles = (int)(cdiv(g.Wl, adj_tile_w(g)) * cdiv(g.Hl, adj_tile_h(g)));
-  if (pl.adj_tiles >= (mf ? target / 4 : target / 2)) {
+  const int group_tiles = g.small16 ? tiles128 : pl.adj_tiles;
+  if (group_tiles >= (mf ? target / 4 : target / 2)) {
     pl.adj_groups = 1;
     pl.adj_fpg = g.n;
   } else {
-    int ag = (int)std::min<int64_t>(g.n, cdiv(target, pl.adj_tiles));
+    int ag = (int)std::min<int64_t>(g.n, cdiv(target, group_tiles));
     ag = std::max(ag, 1);
     pl.adj_fpg = (int)cdiv(g.n, ag);
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
@@ -183,16 +191,12 @@ Plan make_serving_plan(const Geometry& g) {
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
   pl.max_partials = std::max(pl.fwd_tiles * pl.fwd_groups, std::max(pl.adj_tiles, pl.upd_blocks));
   if (uses_mfma(g)) {
-    // the variants em_autotune picks on the large workloads (33 x 4096^2 sr = 1,
-    // 16 x 2048^2 sr = 2) for each encoding (the sr = 1 FP16 forward: 4x2 blocks
-    // per wave with the image fragments loaded ahead; the sr = 2 forward of jobs
-    // with its frames in the N dimension: 4 rows x 2 blocks per wave in the FP16
-    // split form, 4 rows x 1 block in the BF16 split form); for the sr = 2 FP16
-    // adjoint the 4x2-block variant, 3% slower alone but free of scratch reloads
-    // in its batched form
+    // variant 0 but for: the sr = 2 forward of FP16 split jobs (4 rows x 2 blocks
+    // per wave with the frames in the N dimension, 1x4 blocks else), whose batched
+    // form is faster there, and the sr = 1 adjoint of the BF16 forms of small kernels
     const bool f16 = g.precision == EM_FP16_SPLIT;
-    pl.fwd_variant = g.sr == 1 ? (f16 ? 1 : 0) : (uses_m2n(g) ? (f16 ? 1 : 0) : (f16 ? 2 : 0));
-    pl.adj_variant = g.sr == 1 ? 2 : (f16 ? 1 : 0);
+    pl.fwd_variant = g.sr == 2 && f16 ? (uses_m2n(g) ? 1 : 2) : 0;
+    pl.adj_variant = g.sr == 1 && !f16 ? 2 : 0;
   }
   return pl;
 }
@@ -616,6 +620,7 @@ static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   if (serving || !allow_mc32) g.mc32 = 0;
+  if (serving) g.small16 = 0;
   if (g.weight_mode == EM_W_LITERAL && g.sr != 1)
     return fail(EM_ENOTSUP, "the typeset weighting is defined for sr = 1 only");
   const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
@@ -856,7 +861,7 @@ int em_check_plan(const em_problem* p) {
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   for (int serving = 0; serving < 2; ++serving) {
-    if (serving) g.mc32 = 0;
+    if (serving) g.mc32 = g.small16 = 0;
     const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
     em_ctx c{};
     c.g = g;

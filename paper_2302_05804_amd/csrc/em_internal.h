@@ -48,6 +48,8 @@ struct Geometry {
   int64_t Nf, Nl;
   int precision, weight_mode;
   float nu;   // Student-t degrees of freedom (EM_W_STUDENT_T)
+  // FP16 split form, sr = 1, few 128 x 128 tiles: 64 x 64 outputs per workgroup
+  int small16;
   // FP32 form on the matrix cores (em_cell.hip: three bf16 parts of each operand):
   // set by make_geometry where that path is the faster one, cleared where its
   // tables do not fit (serving arenas, the static scratch)
@@ -252,7 +254,7 @@ int mfma_variants();
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band = false);
 int mfma_tile_h(const Geometry& g);   // outputs of a workgroup, sr = 1
-int mfma_tile_w();
+int mfma_tile_w(const Geometry& g);
 size_t mfma_table_bytes(const Geometry& g, int dir);
 
 // Host-side check that a launch grid matches its descriptor: `tiles` tiles of

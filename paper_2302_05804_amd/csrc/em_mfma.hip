@@ -39,6 +39,7 @@
 namespace em {
 
 constexpr int MF_TILE = 128;   // every sr = 1 variant covers 128 x 128 outputs
+constexpr int MF_SMALL = 64;   // or 64 x 64 for small images (FP16 split)
 
 // Tile configuration: each wave owns BR x BC blocks of 16 x 16 outputs, the
 // workgroup WR x WC waves.
@@ -875,8 +876,10 @@ hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd
   return hipGetLastError();
 }
 
-int mfma_tile_h(const Geometry& g) { return uses_cell(g) ? cell_tile_h(g.precision) : MF_TILE; }
-int mfma_tile_w() { return MF_TILE; }
+int mfma_tile_h(const Geometry& g) {
+  return uses_cell(g) ? cell_tile_h(g.precision) : g.small16 ? MF_SMALL : MF_TILE;
+}
+int mfma_tile_w(const Geometry& g) { return g.small16 ? MF_SMALL : MF_TILE; }
 
 size_t mfma_table_bytes(const Geometry& g, int dir) {
   if (g.sr == 2) return dir == 0 && uses_m2n(g) ? mfma2n_table_bytes(g.n) : mfma2_table_bytes(g.n, dir);
@@ -888,49 +891,82 @@ size_t mfma_table_bytes(const Geometry& g, int dir) {
 int mfma_variants() { return 3; }
 
 namespace {
-// variant v: 0 = 4 waves of 4x4 blocks; 1 = 8 waves of 4x2 blocks; 2 = 8 waves of 2x4 blocks
+// Variants 0, 1, 2 of each direction.  Every job starts on variant 0, so that is
+// the one that is fastest on the workloads' sizes (the sums are the same bit for
+// bit in all of them).  FP16 split, K = 43, us per launch of the forward / forward
+// with E-step weights / adjoint on binary16 r / on FP32 r, 16 x 1024^2 and (second
+// and fourth) 12 x 1500 x 1777: 8 waves of 4x2 blocks 133 / 340 / 118 / 328, 8
+// waves of 2x4 blocks 137 / 359 / 116 / 323, 4 waves of 4x4 blocks
+// 165 / 621 / 129 / 427.
+template <int KT, int PREC, int PFT>
+struct MfVariants {
+  using W44 = MfCfg<KT, PREC, 4, 4, 2, 2, 1, PFT>;
+  using W42 = MfCfg<KT, PREC, 4, 2, 2, 4, 0, PFT>;
+  using W24 = MfCfg<KT, PREC, 2, 4, 4, 2, 0, PFT>;
+  // the 4x2-block forward on binary16 r planes loads the next fragment row of the
+  // image before the products of the current one (4% faster there)
+  using W42A = MfCfg<KT, PREC, 4, 2, 2, 4, 1, PFT>;
+  static constexpr bool H = PREC == EM_FP16_SPLIT;
+  using F0 = std::conditional_t<H, W42, W44>;
+  using F1 = std::conditional_t<H, W24, W42>;
+  using F2 = std::conditional_t<H, W44, W24>;
+  using A0 = std::conditional_t<H, W24, W44>;
+  using A1 = W42;
+  using A2 = std::conditional_t<H, W44, W24>;
+  static_assert(W44::TH == MF_TILE && W44::TW == MF_TILE && W42::TH == MF_TILE &&
+                W42::TW == MF_TILE && W24::TH == MF_TILE && W24::TW == MF_TILE, "tile");
+};
+
+// FP16 split on small images: 64 x 64 outputs per workgroup, 8 waves of 2x1
+// blocks.  A job of few tiles is a chain of short launches that each leave most
+// compute units idle; a quarter of the work per wave shortens every one of them.
+template <int KT>
+hipError_t launch_small(int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
+  using C = MfCfg<KT, EM_FP16_SPLIT, 2, 1, 2, 4, 0, 2>;
+  static_assert(C::TH == MF_SMALL && C::TW == MF_SMALL, "tile");
+  const dim3 block(C::NT);
+  if (dir == 0 && a.r16 != nullptr) hipLaunchKernelGGL(mfma_fwd16_kernel<C>, grid, block, 0, s, a);
+  else if (a.r16 != nullptr) hipLaunchKernelGGL(mfma_adj16_kernel<C>, grid, block, 0, s, a);
+  else if (dir == 0 && a.out_y != nullptr) hipLaunchKernelGGL(mfma_fwd_t_kernel<C>, grid, block, 0, s, a);
+  else if (dir == 0) hipLaunchKernelGGL(mfma_fwd_kernel<C>, grid, block, 0, s, a);
+  else hipLaunchKernelGGL(mfma_adj_kernel<C>, grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 template <int KT, int PREC>
 hipError_t launch_dir(int dir, int variant, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
   // Toeplitz fragments: staged in LDS for the one-plane binary16 image (LDS
   // traffic is low there), register prefetch for the two-plane bf16 split
   constexpr int PFT = PREC == EM_FP16_SPLIT ? 2 : 1;
-  using C0 = MfCfg<KT, PREC, 4, 4, 2, 2, 1, PFT>;
-  using C1 = MfCfg<KT, PREC, 4, 2, 2, 4, 0, PFT>;
-  using C2 = MfCfg<KT, PREC, 2, 4, 4, 2, 0, PFT>;
-  static_assert(C0::TH == MF_TILE && C0::TW == MF_TILE, "tile");
-  static_assert(C1::TH == MF_TILE && C1::TW == MF_TILE, "tile");
-  static_assert(C2::TH == MF_TILE && C2::TW == MF_TILE, "tile");
+  using V = MfVariants<KT, PREC, PFT>;
   if constexpr (PREC == EM_FP16_SPLIT) {
     if (a.r16 != nullptr && dir == 0) {
-      // the 4x2-block forward on binary16 r planes loads the next fragment row
-      // of the image before the products of the current one (4% faster there)
-      using C1A = MfCfg<KT, PREC, 4, 2, 2, 4, 1, PFT>;
-      if (variant == 1) hipLaunchKernelGGL(mfma_fwd16_kernel<C1A>, grid, dim3(C1A::NT), 0, s, a);
-      else if (variant == 2) hipLaunchKernelGGL(mfma_fwd16_kernel<C2>, grid, dim3(C2::NT), 0, s, a);
-      else hipLaunchKernelGGL(mfma_fwd16_kernel<C0>, grid, dim3(C0::NT), 0, s, a);
+      if (variant == 1) hipLaunchKernelGGL((mfma_fwd16_kernel<typename V::F1>), grid, dim3(V::F1::NT), 0, s, a);
+      else if (variant == 2) hipLaunchKernelGGL((mfma_fwd16_kernel<typename V::F2>), grid, dim3(V::F2::NT), 0, s, a);
+      else hipLaunchKernelGGL((mfma_fwd16_kernel<typename V::W42A>), grid, dim3(V::W42A::NT), 0, s, a);
       return hipGetLastError();
     }
     if (a.r16 != nullptr) {
-      if (variant == 1) hipLaunchKernelGGL(mfma_adj16_kernel<C1>, grid, dim3(C1::NT), 0, s, a);
-      else if (variant == 2) hipLaunchKernelGGL(mfma_adj16_kernel<C2>, grid, dim3(C2::NT), 0, s, a);
-      else hipLaunchKernelGGL(mfma_adj16_kernel<C0>, grid, dim3(C0::NT), 0, s, a);
+      if (variant == 1) hipLaunchKernelGGL((mfma_adj16_kernel<typename V::A1>), grid, dim3(V::A1::NT), 0, s, a);
+      else if (variant == 2) hipLaunchKernelGGL((mfma_adj16_kernel<typename V::A2>), grid, dim3(V::A2::NT), 0, s, a);
+      else hipLaunchKernelGGL((mfma_adj16_kernel<typename V::A0>), grid, dim3(V::A0::NT), 0, s, a);
       return hipGetLastError();
     }
   } else {
     if (a.r16 != nullptr) return hipErrorInvalidValue;
   }
   if (dir == 0 && a.out_y != nullptr) {
-    if (variant == 1) hipLaunchKernelGGL(mfma_fwd_t_kernel<C1>, grid, dim3(C1::NT), 0, s, a);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_t_kernel<C2>, grid, dim3(C2::NT), 0, s, a);
-    else hipLaunchKernelGGL(mfma_fwd_t_kernel<C0>, grid, dim3(C0::NT), 0, s, a);
+    if (variant == 1) hipLaunchKernelGGL((mfma_fwd_t_kernel<typename V::F1>), grid, dim3(V::F1::NT), 0, s, a);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_fwd_t_kernel<typename V::F2>), grid, dim3(V::F2::NT), 0, s, a);
+    else hipLaunchKernelGGL((mfma_fwd_t_kernel<typename V::F0>), grid, dim3(V::F0::NT), 0, s, a);
   } else if (dir == 0) {
-    if (variant == 1) hipLaunchKernelGGL(mfma_fwd_kernel<C1>, grid, dim3(C1::NT), 0, s, a);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_kernel<C2>, grid, dim3(C2::NT), 0, s, a);
-    else hipLaunchKernelGGL(mfma_fwd_kernel<C0>, grid, dim3(C0::NT), 0, s, a);
+    if (variant == 1) hipLaunchKernelGGL((mfma_fwd_kernel<typename V::F1>), grid, dim3(V::F1::NT), 0, s, a);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_fwd_kernel<typename V::F2>), grid, dim3(V::F2::NT), 0, s, a);
+    else hipLaunchKernelGGL((mfma_fwd_kernel<typename V::F0>), grid, dim3(V::F0::NT), 0, s, a);
   } else {
-    if (variant == 1) hipLaunchKernelGGL(mfma_adj_kernel<C1>, grid, dim3(C1::NT), 0, s, a);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_adj_kernel<C2>, grid, dim3(C2::NT), 0, s, a);
-    else hipLaunchKernelGGL(mfma_adj_kernel<C0>, grid, dim3(C0::NT), 0, s, a);
+    if (variant == 1) hipLaunchKernelGGL((mfma_adj_kernel<typename V::A1>), grid, dim3(V::A1::NT), 0, s, a);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_adj_kernel<typename V::A2>), grid, dim3(V::A2::NT), 0, s, a);
+    else hipLaunchKernelGGL((mfma_adj_kernel<typename V::A0>), grid, dim3(V::A0::NT), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -943,38 +979,35 @@ hipError_t launch_dir_batched(int dir, int variant, int grid, const MfmaLaunch* 
   // Toeplitz fragments: staged in LDS for the one-plane binary16 image (LDS
   // traffic is low there), register prefetch for the two-plane bf16 split
   constexpr int PFT = PREC == EM_FP16_SPLIT ? 2 : 1;
-  using C0 = MfCfg<KT, PREC, 4, 4, 2, 2, 1, PFT>;
-  using C1 = MfCfg<KT, PREC, 4, 2, 2, 4, 0, PFT>;
-  using C2 = MfCfg<KT, PREC, 2, 4, 4, 2, 0, PFT>;
+  using V = MfVariants<KT, PREC, PFT>;
   if constexpr (PREC == EM_FP16_SPLIT) {
     if (r16 && dir == 0) {
-      using C1A = MfCfg<KT, PREC, 4, 2, 2, 4, 1, PFT>;   // as in launch_dir
-      if (variant == 1) hipLaunchKernelGGL(mfma_fwd16_batched<C1A>, dim3(grid), dim3(C1A::NT), 0, s, d, it, n);
-      else if (variant == 2) hipLaunchKernelGGL(mfma_fwd16_batched<C2>, dim3(grid), dim3(C2::NT), 0, s, d, it, n);
-      else hipLaunchKernelGGL(mfma_fwd16_batched<C0>, dim3(grid), dim3(C0::NT), 0, s, d, it, n);
+      if (variant == 1) hipLaunchKernelGGL((mfma_fwd16_batched<typename V::F1>), dim3(grid), dim3(V::F1::NT), 0, s, d, it, n);
+      else if (variant == 2) hipLaunchKernelGGL((mfma_fwd16_batched<typename V::F2>), dim3(grid), dim3(V::F2::NT), 0, s, d, it, n);
+      else hipLaunchKernelGGL((mfma_fwd16_batched<typename V::W42A>), dim3(grid), dim3(V::W42A::NT), 0, s, d, it, n);
       return hipGetLastError();
     }
     if (r16) {
-      if (variant == 1) hipLaunchKernelGGL(mfma_adj16_batched<C1>, dim3(grid), dim3(C1::NT), 0, s, d, it, n);
-      else if (variant == 2) hipLaunchKernelGGL(mfma_adj16_batched<C2>, dim3(grid), dim3(C2::NT), 0, s, d, it, n);
-      else hipLaunchKernelGGL(mfma_adj16_batched<C0>, dim3(grid), dim3(C0::NT), 0, s, d, it, n);
+      if (variant == 1) hipLaunchKernelGGL((mfma_adj16_batched<typename V::A1>), dim3(grid), dim3(V::A1::NT), 0, s, d, it, n);
+      else if (variant == 2) hipLaunchKernelGGL((mfma_adj16_batched<typename V::A2>), dim3(grid), dim3(V::A2::NT), 0, s, d, it, n);
+      else hipLaunchKernelGGL((mfma_adj16_batched<typename V::A0>), dim3(grid), dim3(V::A0::NT), 0, s, d, it, n);
       return hipGetLastError();
     }
   } else {
     if (r16) return hipErrorInvalidValue;
   }
   if (dir == 0 && robust) {
-    if (variant == 1) hipLaunchKernelGGL(mfma_fwd_t_batched<C1>, dim3(grid), dim3(C1::NT), 0, s, d, it, n);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_t_batched<C2>, dim3(grid), dim3(C2::NT), 0, s, d, it, n);
-    else hipLaunchKernelGGL(mfma_fwd_t_batched<C0>, dim3(grid), dim3(C0::NT), 0, s, d, it, n);
+    if (variant == 1) hipLaunchKernelGGL((mfma_fwd_t_batched<typename V::F1>), dim3(grid), dim3(V::F1::NT), 0, s, d, it, n);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_fwd_t_batched<typename V::F2>), dim3(grid), dim3(V::F2::NT), 0, s, d, it, n);
+    else hipLaunchKernelGGL((mfma_fwd_t_batched<typename V::F0>), dim3(grid), dim3(V::F0::NT), 0, s, d, it, n);
   } else if (dir == 0) {
-    if (variant == 1) hipLaunchKernelGGL(mfma_fwd_batched<C1>, dim3(grid), dim3(C1::NT), 0, s, d, it, n);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_fwd_batched<C2>, dim3(grid), dim3(C2::NT), 0, s, d, it, n);
-    else hipLaunchKernelGGL(mfma_fwd_batched<C0>, dim3(grid), dim3(C0::NT), 0, s, d, it, n);
+    if (variant == 1) hipLaunchKernelGGL((mfma_fwd_batched<typename V::F1>), dim3(grid), dim3(V::F1::NT), 0, s, d, it, n);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_fwd_batched<typename V::F2>), dim3(grid), dim3(V::F2::NT), 0, s, d, it, n);
+    else hipLaunchKernelGGL((mfma_fwd_batched<typename V::F0>), dim3(grid), dim3(V::F0::NT), 0, s, d, it, n);
   } else {
-    if (variant == 1) hipLaunchKernelGGL(mfma_adj_batched<C1>, dim3(grid), dim3(C1::NT), 0, s, d, it, n);
-    else if (variant == 2) hipLaunchKernelGGL(mfma_adj_batched<C2>, dim3(grid), dim3(C2::NT), 0, s, d, it, n);
-    else hipLaunchKernelGGL(mfma_adj_batched<C0>, dim3(grid), dim3(C0::NT), 0, s, d, it, n);
+    if (variant == 1) hipLaunchKernelGGL((mfma_adj_batched<typename V::A1>), dim3(grid), dim3(V::A1::NT), 0, s, d, it, n);
+    else if (variant == 2) hipLaunchKernelGGL((mfma_adj_batched<typename V::A2>), dim3(grid), dim3(V::A2::NT), 0, s, d, it, n);
+    else hipLaunchKernelGGL((mfma_adj_batched<typename V::A0>), dim3(grid), dim3(V::A0::NT), 0, s, d, it, n);
   }
   return hipGetLastError();
 }
@@ -1013,7 +1046,7 @@ bool mfma_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaL
     return false;
   if (g.sr == 2) return mfma2_desc_ok(g, dir, tiles, groups, a);
   return a.H == g.Hl && a.W == g.Wl &&
-         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g), MF_TILE);
+         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g), mfma_tile_w(g));
 }
 
 int r16_pitch(const Geometry& g) {
@@ -1069,30 +1102,55 @@ hipError_t launch_lo_band_check(const Geometry& g, const float* psf, int* flag, 
   return hipGetLastError();
 }
 
-// Zero the r16 planes (16 bytes per thread).
-__global__ __launch_bounds__(256) void r16_clear_kernel(uint4* p, int64_t count) {
+// Zero the r16 planes (16 bytes per thread) and the frames' largest weights.
+__global__ __launch_bounds__(256) void r16_clear_kernel(uint4* p, int64_t count, float* umax,
+                                                        int n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count;
        i += (int64_t)gridDim.x * 256)
     p[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (blockIdx.x == 0)
+    for (int t = threadIdx.x; t < n; t += 256) umax[t] = 0.f;
 }
 
-// Per frame (one block each): the largest weight u_t and the sum of the absolute
-// taps the forward applies (f_t, or for sr = 2 the 2x2 box-extended kernel,
-// whose sum is fscale = 4 times that of f_t).
+// Largest |x[i]| over this thread's share of a pass by `nb` blocks, of which this is
+// block `b`: 16-byte loads, four in flight per thread, when x is 16-byte aligned.
+__device__ inline float abs_max_share(const float* __restrict__ x, int64_t count, int b, int nb) {
+  const int64_t tid = (int64_t)b * blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)nb * blockDim.x;
+  float m = 0.f;
+  int64_t done = 0;
+  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
+    const float4* x4 = reinterpret_cast<const float4*>(x);
+    const int64_t n4 = count >> 2;
+#pragma unroll 4
+    for (int64_t i = tid; i < n4; i += stride) {
+      const float4 v = x4[i];
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    }
+    done = n4 << 2;
+  }
+  for (int64_t i = done + tid; i < count; i += stride) m = fmaxf(m, fabsf(x[i]));
+  return m;
+}
+
+// Per frame (blockIdx.y): the largest weight u_t, and from the frame's first block
+// the sum of the absolute taps the forward applies (f_t, or for sr = 2 the 2x2
+// box-extended kernel, whose sum is fscale = 4 times that of f_t).  u >= 0, so its
+// bits order as integers and the blocks of a frame meet in an atomic maximum.
+// HBM-bound (u once); with one block per frame 16 x 1024^2 took 361 us.
 __global__ __launch_bounds__(1024) void r16_frame_stats_kernel(const float* u, int64_t Nf,
                                                                const float* psf, int K,
                                                                float fscale, float* umax,
                                                                float* fsum) {
   __shared__ float redm[16];
   __shared__ double reds[16];
-  const int t = blockIdx.x;
-  const float* ut = u + (int64_t)t * Nf;
-  float m = 0.f;
-  for (int64_t i = threadIdx.x; i < Nf; i += 1024) m = fmaxf(m, ut[i]);
+  const int t = blockIdx.y;
+  float m = wave_max(abs_max_share(u + (int64_t)t * Nf, Nf, blockIdx.x, gridDim.x));
   double sf = 0.0;
-  for (int i = threadIdx.x; i < K * K; i += 1024) sf += fabs((double)psf[(int64_t)t * K * K + i]);
-  m = wave_max(m);
-  for (int off = 32; off > 0; off >>= 1) sf += __shfl_xor(sf, off, 64);
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < K * K; i += 1024) sf += fabs((double)psf[(int64_t)t * K * K + i]);
+    for (int off = 32; off > 0; off >>= 1) sf += __shfl_xor(sf, off, 64);
+  }
   if ((threadIdx.x & 63) == 0) {
     redm[threadIdx.x >> 6] = m;
     reds[threadIdx.x >> 6] = sf;
@@ -1105,36 +1163,15 @@ __global__ __launch_bounds__(1024) void r16_frame_stats_kernel(const float* u, i
       mm = fmaxf(mm, redm[i]);
       ss += reds[i];
     }
-    umax[t] = mm;
-    fsum[t] = (float)(ss * fscale);
+    atomicMax(reinterpret_cast<int*>(umax + t), __float_as_int(mm));
+    if (blockIdx.x == 0) fsum[t] = (float)(ss * fscale);
   }
 }
 
 // Block maxima of x (R16_XBLOCKS blocks, grid-stride).
-// Largest |x[i]| over this thread's share of a grid-stride pass: 16-byte loads,
-// four in flight per thread, when x is 16-byte aligned.
-__device__ inline float abs_max_share(const float* __restrict__ x, int64_t Nl) {
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  float m = 0.f;
-  int64_t done = 0;
-  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    const float4* x4 = reinterpret_cast<const float4*>(x);
-    const int64_t n4 = Nl >> 2;
-#pragma unroll 4
-    for (int64_t i = tid; i < n4; i += stride) {
-      const float4 v = x4[i];
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-    }
-    done = n4 << 2;
-  }
-  for (int64_t i = done + tid; i < Nl; i += stride) m = fmaxf(m, fabsf(x[i]));
-  return m;
-}
-
 __global__ __launch_bounds__(256) void r16_xmax_kernel(const float* x, int64_t Nl, float* part) {
   __shared__ float red[4];
-  float m = abs_max_share(x, Nl);
+  float m = abs_max_share(x, Nl, blockIdx.x, gridDim.x);
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -1163,7 +1200,7 @@ __global__ __launch_bounds__(256) void r16_scale_kernel(const float* part, int n
 __global__ __launch_bounds__(256) void r16_xmax_batched_kernel(const R16Job* jobs) {
   __shared__ float red[4];
   const R16Job j = jobs[blockIdx.y];
-  float m = abs_max_share(j.x, j.Nl);
+  float m = abs_max_share(j.x, j.Nl, blockIdx.x, gridDim.x);
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -1195,8 +1232,11 @@ hipError_t launch_r16_setup(const Geometry& g, const float* u, const float* psf,
   const int64_t n16 = halves / 8;
   const int blocks = (int)std::min<int64_t>(8192, (n16 + 255) / 256);
   hipLaunchKernelGGL(r16_clear_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, s,
-                     reinterpret_cast<uint4*>(r16), n16);
-  hipLaunchKernelGGL(r16_frame_stats_kernel, dim3(g.n), dim3(1024), 0, s, u, g.Nf, psf, g.K,
+                     reinterpret_cast<uint4*>(r16), n16, umax, g.n);
+  // about 2048 blocks in all, at least 16 K pixels each
+  const int per_frame = (int)std::max<int64_t>(
+      1, std::min<int64_t>(std::max(1, 2048 / g.n), g.Nf / 16384));
+  hipLaunchKernelGGL(r16_frame_stats_kernel, dim3(per_frame, g.n), dim3(1024), 0, s, u, g.Nf, psf, g.K,
                      g.sr == 2 ? 4.f : 1.f, umax, fsum);
   return hipGetLastError();
 }
@@ -1222,6 +1262,8 @@ hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int g
     default: return hipErrorInvalidValue;                                    \
   }
   if (uses_cell(g)) return launch_cell(g.precision, dir, grid, a, s);
+  if (g.small16)
+    return g.KT == KT_LARGE ? launch_small<KT_LARGE>(dir, grid, a, s) : launch_small<KT_SMALL>(dir, grid, a, s);
   if (g.KT == KT_LARGE)
     return g.precision == EM_FP16_SPLIT ? launch_dir<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, a, s)
                                         : hipErrorInvalidValue;
