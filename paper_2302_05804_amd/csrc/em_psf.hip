@@ -53,51 +53,111 @@ struct PsfShape {
   static constexpr int NMAT = 8;              // A, At, F, R, Tt, Ut, H0, H1
 };
 
-// C block (bm, bn) of L * R with R given transposed (Rt[n][k]): lane i supplies
-// L[16 bm + i%16][k] and Rt[16 bn + i%16][k] for the k values of its lane group
-// g = i/16, k in [g KS, g KS + KS).  The matrix instruction sums its four lane
-// groups, so every k is taken once.  Returns C[16 bm + 4 g + j][16 bn + i%16]
-// in element j.
+// A lane's share of one row of an operand: the k values of its lane group.
 template <int KP>
-__device__ inline psf_f32x4 psf_block(const float* L, const float* Rt, int bm, int bn) {
-  using S = PsfShape<KP>;
-  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  const float* lp = L + (16 * bm + r) * S::PP + g * S::KS;
-  const float* rp = Rt + (16 * bn + r) * S::PP + g * S::KS;
+struct PsfRow {
+  float4 v[PsfShape<KP>::KS / 4];
+  // row 16 blk + lane%16 of a matrix
+  __device__ void load(const float* M, int blk) {
+    using S = PsfShape<KP>;
+    const int lane = threadIdx.x & 63;
+    const float* p = M + (16 * blk + (lane & 15)) * S::PP + (lane >> 4) * S::KS;
+#pragma unroll
+    for (int c = 0; c < S::KS / 4; ++c) v[c] = *reinterpret_cast<const float4*>(p + 4 * c);
+  }
+};
+
+// C block of L * R with R given transposed (Rt[n][k]): lane i supplies L[i%16][k] and
+// Rt[i%16][k] of the block's rows for the k values of its lane group g = i/16, k
+// in [g KS, g KS + KS).  The matrix instruction sums its four lane groups, so every
+// k is taken once.  Returns C[4 g + j][i%16] of the block in element j.
+template <int KP>
+__device__ inline psf_f32x4 psf_block(const PsfRow<KP>& L, const PsfRow<KP>& Rt) {
   // four independent accumulators, so that consecutive matrix instructions do
   // not wait for each other's results
   psf_f32x4 acc[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) acc[e] = psf_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < S::KS; c += 4) {
-    const float4 a4 = *reinterpret_cast<const float4*>(lp + c);
-    const float4 b4 = *reinterpret_cast<const float4*>(rp + c);
-    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.x, b4.x, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, b4.y, acc[1], 0, 0, 0);
-    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, b4.z, acc[2], 0, 0, 0);
-    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, b4.w, acc[3], 0, 0, 0);
+  for (int c = 0; c < PsfShape<KP>::KS / 4; ++c) {
+    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.v[c].x, Rt.v[c].x, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.v[c].y, Rt.v[c].y, acc[1], 0, 0, 0);
+    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.v[c].z, Rt.v[c].z, acc[2], 0, 0, 0);
+    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.v[c].w, Rt.v[c].w, acc[3], 0, 0, 0);
   }
   return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
+// The rows of A and A^T that a wave multiplies by in every step (its block's row
+// bm and column bn).  Up to 48 x 48 they stay in registers for the whole run, which
+// leaves one operand of each product to LDS (16 x 43^2, 2000 steps: 8.24 -> 7.80 ms with
+// the neighbours of h read early and the shared divisors); at
+// 64 x 64, with 16 waves of 128 registers, they would spill and are read each time.
+template <int KP>
+struct PsfFixed {
+  static constexpr bool HELD = KP <= 48;
+  PsfRow<KP> rows[HELD ? 4 : 1];   // A bm, A bn, A^T bm, A^T bn
+  const float *A, *At;
+  int bm, bn;
+  psf_f32x4 f;                     // f at the lane's four residual pixels
+  __device__ PsfFixed(const float* A_, const float* At_, const float* F, int bm_, int bn_)
+      : A(A_), At(At_), bm(bm_), bn(bn_) {
+    using S = PsfShape<KP>;
+    if constexpr (HELD) {
+      rows[0].load(A, bm);
+      rows[1].load(A, bn);
+      rows[2].load(At, bm);
+      rows[3].load(At, bn);
+    }
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = F[(16 * bm + 4 * (lane >> 4) + j) * S::PP + 16 * bn + (lane & 15)];
+  }
+  template <int WHICH>
+  __device__ PsfRow<KP> row() const {
+    if constexpr (HELD) {
+      return rows[WHICH];
+    } else {
+      PsfRow<KP> v;
+      v.load(WHICH < 2 ? A : At, WHICH % 2 == 0 ? bm : bn);
+      return v;
+    }
+  }
+};
+
 // Tt = (h A^T)^T, then R = A T - F (pads stay 0: A and F are 0 there).
 template <int KP>
-__device__ inline void psf_residual(const float* A, const float* H, const float* F, float* Tt,
-                                    float* R, int bm, int bn) {
+__device__ inline void psf_residual(const PsfFixed<KP>& X, const float* H, float* Tt, float* R,
+                                    int bm, int bn) {
   using S = PsfShape<KP>;
   const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  const psf_f32x4 t = psf_block<KP>(H, A, bm, bn);            // T[a][J], a = 16bm+4g+j
+  PsfRow<KP> v;
+  v.load(H, bm);
+  const psf_f32x4 t = psf_block<KP>(v, X.template row<1>());                 // T[a][J], a = 16bm+4g+j
   *reinterpret_cast<psf_f32x4*>(Tt + (16 * bn + r) * S::PP + 16 * bm + 4 * g) = t;
   __syncthreads();
-  const psf_f32x4 m = psf_block<KP>(A, Tt, bm, bn);           // M[I][J], I = 16bm+4g+j
+  v.load(Tt, bn);
+  const psf_f32x4 m = psf_block<KP>(X.template row<0>(), v);                 // M[I][J], I = 16bm+4g+j
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int o = (16 * bm + 4 * g + j) * S::PP + 16 * bn + r;
-    R[o] = m[j] - F[o];
-  }
+  for (int j = 0; j < 4; ++j) R[(16 * bm + 4 * g + j) * S::PP + 16 * bn + r] = m[j] - X.f[j];
   __syncthreads();
 }
+
+// Correctly rounded v / c for a divisor shared by many quotients, from its correctly
+// rounded reciprocal rc and two fused steps (Markstein, 1990); a divisor whose
+// significand is all ones, where those need not round correctly, divides.
+struct PsfDivisor {
+  float c, rc;
+  bool plain;
+  __device__ explicit PsfDivisor(float c_)
+      : c(c_), rc(1.f / c_), plain((__float_as_uint(c_) & 0x7fffffu) == 0x7fffffu) {}
+  __device__ float divide(float v) const {
+    // quotients and remainders stay normal: below that, divide
+    if (plain || !(fabsf(v) > 1e-30f)) return v / c;
+    const float q = v * rc;
+    return fmaf(fmaf(-q, c, v), rc, q);
+  }
+};
 
 template <int KP>
 __global__ __launch_bounds__(PsfShape<KP>::NT) void psf_fit_kernel(PsfParams P,
@@ -175,37 +235,52 @@ __global__ __launch_bounds__(PsfShape<KP>::NT) void psf_fit_kernel(PsfParams P,
   double lrk_d = (double)P.lr * (double)fmax;
   const double rdec = P.S > 1 ? exp(log((double)P.decay) / (double)(P.S - 1)) : 1.0;
   const float b1 = P.b1, b2 = P.b2, eps = P.eps, lam2 = 2.f * P.lam;
-  const int b = 16 * bn + r;
+  const int b = 16 * bn + r, a0 = 16 * bm + 4 * g;
   double b1k = 1.0, b2k = 1.0;
+  const PsfFixed<KP> X(A, At, F, bm, bn);
+  float hv[4];   // h at the lane's four pixels
+#pragma unroll
+  for (int j = 0; j < 4; ++j) hv[j] = Hc[(a0 + j) * S::PP + b];
   for (int k = 1; k <= P.S; ++k) {
-    psf_residual<KP>(A, Hc, F, Tt, R, bm, bn);
-    // U = rho A, stored transposed (Ut[b][I])
-    const psf_f32x4 u = psf_block<KP>(R, At, bm, bn);
-    *reinterpret_cast<psf_f32x4*>(Ut + (16 * bn + r) * S::PP + 16 * bm + 4 * g) = u;
-    __syncthreads();
-    // gradient 2 A^T U + 2 lambda L h, Adam, projection
-    const psf_f32x4 gd = psf_block<KP>(At, Ut, bm, bn);
+    // h around the lane's pixels (h is 0 in the pads)
+    const float up = a0 > 0 ? Hc[(a0 - 1) * S::PP + b] : 0.f;
+    const float down = a0 + 4 < KP ? Hc[(a0 + 4) * S::PP + b] : 0.f;
+    float left[4], right[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      left[j] = b > 0 ? Hc[(a0 + j) * S::PP + b - 1] : 0.f;
+      right[j] = Hc[(a0 + j) * S::PP + b + 1];
+    }
     b1k *= (double)b1;
     b2k *= (double)b2;
     const float lrk = (float)lrk_d;
     lrk_d *= rdec;
-    const float c1 = (float)(1.0 - b1k), c2 = (float)(1.0 - b2k);
+    const PsfDivisor c1((float)(1.0 - b1k)), c2((float)(1.0 - b2k));
+    psf_residual<KP>(X, Hc, Tt, R, bm, bn);
+    // U = rho A, stored transposed (Ut[b][I])
+    PsfRow<KP> v;
+    v.load(R, bm);
+    const psf_f32x4 u = psf_block<KP>(v, X.template row<3>());
+    *reinterpret_cast<psf_f32x4*>(Ut + (16 * bn + r) * S::PP + 16 * bm + 4 * g) = u;
+    __syncthreads();
+    // gradient 2 A^T U + 2 lambda L h, Adam, projection
+    v.load(Ut, bn);
+    const psf_f32x4 gd = psf_block<KP>(X.template row<2>(), v);
+    const float old[4] = {hv[0], hv[1], hv[2], hv[3]};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int a = 16 * bm + 4 * g + j;
+      const int a = a0 + j;
       float hn = 0.f;
       if (a < kh && b < kh) {
-        const float hv = Hc[a * S::PP + b];
-        const float nb = (a > 0 ? Hc[(a - 1) * S::PP + b] : 0.f) +
-                         (a + 1 < kh ? Hc[(a + 1) * S::PP + b] : 0.f) +
-                         (b > 0 ? Hc[a * S::PP + b - 1] : 0.f) +
-                         (b + 1 < kh ? Hc[a * S::PP + b + 1] : 0.f);
-        const float gr = 2.f * gd[j] + lam2 * (4.f * hv - nb);
+        const float nb = (j > 0 ? old[j > 0 ? j - 1 : 0] : up) + (j < 3 ? old[j < 3 ? j + 1 : 3] : down) +
+                         left[j] + right[j];
+        const float gr = 2.f * gd[j] + lam2 * (4.f * old[j] - nb);
         m1[j] = b1 * m1[j] + (1.f - b1) * gr;
         m2[j] = b2 * m2[j] + (1.f - b2) * gr * gr;
-        const float step = lrk * (m1[j] / c1) / (sqrtf(m2[j] / c2) + eps);
-        hn = fmaxf(hv - step, 0.f);
+        const float step = lrk * c1.divide(m1[j]) / (sqrtf(c2.divide(m2[j])) + eps);
+        hn = fmaxf(old[j] - step, 0.f);
       }
+      hv[j] = hn;
       Hn[a * S::PP + b] = hn;
     }
     __syncthreads();
@@ -217,7 +292,7 @@ __global__ __launch_bounds__(PsfShape<KP>::NT) void psf_fit_kernel(PsfParams P,
   float* ht = hout + (size_t)t * kh * kh;
   for (int q = tid; q < kh * kh; q += S::NT) ht[q] = Hc[(q / kh) * S::PP + q % kh];
   if (objective) {
-    psf_residual<KP>(A, Hc, F, Tt, R, bm, bn);
+    psf_residual<KP>(X, Hc, Tt, R, bm, bn);
     double part = 0.0;
     for (int q = tid; q < kf * kf; q += S::NT) {
       const double rr = (double)R[(q / kf) * S::PP + q % kf];
