@@ -89,6 +89,8 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   // 128 x 128 tiles over all frames
   g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 &&
                cdiv(g->Hf, 128) * cdiv(g->Wf, 128) * g->n <= 128;
+  g->small32 = p->precision == EM_FP32 && !g->mc32 && g->sr == 1 &&
+               cdiv(g->Hf, 64) * cdiv(g->Wf, 64) * g->n <= 256;
   if ((int64_t)g->n * g->Nf > ((int64_t)1 << 40)) { *why = "problem too large"; return false; }
   if (g->Nl >= ((int64_t)1 << 31)) { *why = "latent image of 2^31 pixels or more"; return false; }
   return true;
@@ -127,10 +129,11 @@ Plan make_plan(const Geometry& g) {
     pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w(g)) * cdiv(g.Hf, mfma_tile_h(g)));
   else
     pl.fwd_tiles = (int)(cdiv(g.Wf, fwd_tile_w(g)) * cdiv(g.Hf, fwd_tile_h(g)));
-  // 64 x 64 tiles keep the frame groups of 128 x 128 ones (and with them the order
-  // of the frame sum)
-  const int tiles128 = (int)(cdiv(g.Wf, 128) * cdiv(g.Hf, 128));
-  int fg = (int)std::min<int64_t>(g.n, cdiv(target, g.small16 ? tiles128 : pl.fwd_tiles));
+  // the smaller tiles of small images keep the frame groups of the large ones (and
+  // with them the order of the frame sum)
+  const int side = g.small16 ? 128 : 64;
+  const int large = g.small16 || g.small32 ? (int)(cdiv(g.Wf, side) * cdiv(g.Hf, side)) : 0;
+  int fg = (int)std::min<int64_t>(g.n, cdiv(target, large ? large : pl.fwd_tiles));
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
   if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, g.n));
@@ -144,7 +147,7 @@ Plan make_plan(const Geometry& g) {
     pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w(g)) * cdiv(g.Hl, mfma_tile_h(g)));
   else
     pl.adj_tiles = (int)(cdiv(g.Wl, adj_tile_w(g)) * cdiv(g.Hl, adj_tile_h(g)));
-  const int group_tiles = g.small16 ? tiles128 : pl.adj_tiles;
+  const int group_tiles = large ? large : pl.adj_tiles;
   if (group_tiles >= (mf ? target / 4 : target / 2)) {
     pl.adj_groups = 1;
     pl.adj_fpg = g.n;
@@ -620,7 +623,7 @@ static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   if (serving || !allow_mc32) g.mc32 = 0;
-  if (serving) g.small16 = 0;
+  if (serving) g.small16 = g.small32 = 0;
   if (g.weight_mode == EM_W_LITERAL && g.sr != 1)
     return fail(EM_ENOTSUP, "the typeset weighting is defined for sr = 1 only");
   const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
@@ -861,7 +864,7 @@ int em_check_plan(const em_problem* p) {
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   for (int serving = 0; serving < 2; ++serving) {
-    if (serving) g.mc32 = g.small16 = 0;
+    if (serving) g.mc32 = g.small16 = g.small32 = 0;
     const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
     em_ctx c{};
     c.g = g;

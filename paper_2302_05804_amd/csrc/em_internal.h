@@ -50,6 +50,8 @@ struct Geometry {
   float nu;   // Student-t degrees of freedom (EM_W_STUDENT_T)
   // FP16 split form, sr = 1, few 128 x 128 tiles: 64 x 64 outputs per workgroup
   int small16;
+  // FP32 direct convolution, sr = 1, few 64 x 64 tiles: 16 rows per workgroup
+  int small32;
   // FP32 form on the matrix cores (em_cell.hip: three bf16 parts of each operand):
   // set by make_geometry where that path is the faster one, cleared where its
   // tables do not fit (serving arenas, the static scratch)
