@@ -67,9 +67,9 @@ extern "C" {
 
 /* arithmetic of the two convolutions (the update is always FP32, the
  * log-likelihood and convergence sums always FP64) */
-#define EM_FP32        0    /* products and sums of binary32 accuracy.  sr = 1,
-                               15 < K <= 43, frames of 16384 pixels and more,
-                               not served: on the matrix cores, each operand as
+#define EM_FP32        0    /* products and sums of binary32 accuracy.
+                               15 < K <= 43, 16384 latent pixels and more, not
+                               served: on the matrix cores, each operand as
                                the exact sum of three bf16 parts, six of their
                                nine products (the others are below 2^-24 of the
                                whole one), summed in FP32 in levels; measured

@@ -82,9 +82,9 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   g->precision = p->precision;
   g->weight_mode = p->weight_mode;
   g->nu = p->weight_mode == EM_W_STUDENT_T ? p->nu : 0.f;
-  // FP32 on the matrix cores: from frames of 128 x 128 pixels on (below, the
-  // tables of a frame, 432 KB, would be most of the workspace)
-  g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->sr == 1 && g->Nf >= 128 * 128;
+  // FP32 on the matrix cores: from 128 x 128 latent pixels on (below, the tables of
+  // a frame, 432 KB for sr = 1 and 108 KB for sr = 2, would be most of the workspace)
+  g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->Nl >= 128 * 128;
   // small images in the FP16 split form: up to half the compute units' worth of
   // 128 x 128 tiles over all frames
   g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 &&
@@ -122,6 +122,8 @@ Plan make_plan(const Geometry& g) {
   const bool mf = uses_mfma(g);
   if (uses_m2n(g))
     pl.fwd_tiles = (int)(cdiv(g.Wf, m2n_tile_w(g.precision)) * cdiv(g.Hf, M2N_TH));
+  else if (uses_cell2(g))
+    pl.fwd_tiles = (int)(cdiv(g.Wf, cell2_fwd_tile_w()) * cdiv(g.Hf, cell2_fwd_tile_h()));
   else if (mf && g.sr == 2)
     pl.fwd_tiles = (int)(cdiv(g.Wf, mfma2_fwd_tile_w(g.precision)) *
                          cdiv(g.Hf, mfma2_fwd_tile_h(g.precision)));
@@ -137,10 +139,16 @@ Plan make_plan(const Geometry& g) {
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
   if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, g.n));
+  if (uses_cell2(g)) {   // four frames to a product
+    const int quads = (int)cdiv(g.n, 4);
+    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, quads));
+  }
   if (uses_m2n(g)) pl.fwd_fpg = M2N_FPG;   // the frames are the products' N dimension
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
   pl.adj_variant = 0;
-  if (mf && g.sr == 2)
+  if (uses_cell2(g))
+    pl.adj_tiles = (int)(cdiv(g.Wl, cell2_adj_tile_w()) * cdiv(g.Hl, cell2_adj_tile_h()));
+  else if (mf && g.sr == 2)
     pl.adj_tiles = (int)(cdiv(g.Wl, mfma2_adj_tile_w(g.precision)) *
                          cdiv(g.Hl, mfma2_adj_tile_h(g.precision)));
   else if (mf)
@@ -157,7 +165,7 @@ Plan make_plan(const Geometry& g) {
     pl.adj_fpg = (int)cdiv(g.n, ag);
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
   }
-  if (uses_cell(g)) {
+  if (uses_cell(g) || uses_cell2(g)) {
     // never more partial planes than the rule above holds, which the split forms'
     // workspaces have always had
     const int most = g.mc32 ? std::min(g.n, 16) : pl.adj_groups;

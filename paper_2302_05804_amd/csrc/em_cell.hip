@@ -15,134 +15,6 @@ namespace {
 template <int PREC, bool BAND>
 using CellOf = CellCfg<CellForm<PREC, BAND>, PREC == EM_FP32 ? 4 : 8, 4, 2>;
 
-// Position of this lane: cell row pr of its outputs, its cell's first column.
-struct CellLane {
-  int row0, col;   // image row of group 0's outputs of this lane, first of 4 columns
-};
-
-template <class C>
-__device__ inline CellLane cell_lane(int k0, int l0) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  return {k0 + (w / C::WC) * 4 * C::G + (lane >> 4), l0 + (w % C::WC) * 64 + 4 * (lane & 15)};
-}
-
-// Offsets (halves) of this lane's window in a staged plane: main and tail chunk.
-template <class C>
-__device__ inline int cell_main_off() {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  return (w / C::WC) * 4 * C::G * C::PITCH + (w % C::WC) * 64 + 4 * (lane & 15) + 8 * (lane >> 4);
-}
-template <class C>
-__device__ inline int cell_tail_off() {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gq = lane >> 4;
-  return (w / C::WC) * 4 * C::G * C::PITCH + (w % C::WC) * 64 + 4 * (lane & 15) +
-         (gq >> 1) * 4 * C::PITCH + 32 + 8 * (gq & 1);
-}
-
-__device__ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-// Four consecutive values of row `row` from column `col` (clamped into the
-// image; a clamped value is never used).
-__device__ inline void load4(const float* __restrict__ p, int row, int col, int H, int W, bool vec,
-                             float (&v)[4]) {
-  const int64_t base = (int64_t)min(row, H - 1) * W;
-  if (vec) {
-    const float4 q = *reinterpret_cast<const float4*>(p + base + col);
-    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = p[base + min(col + i, W - 1)];
-  }
-}
-__device__ inline void store4(float* __restrict__ p, int row, int col, int W, bool vec,
-                              const float (&v)[4]) {
-  float* q = p + (int64_t)row * W + col;
-  if (vec) {
-    *reinterpret_cast<float4*>(q) = make_float4(v[0], v[1], v[2], v[3]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (col + i < W) q[i] = v[i];
-  }
-}
-
-// The image tile of a workgroup on its way into the LDS planes: raw pixels in
-// registers, then split and stored.  A wave takes the rows w, w + NW, ... of the
-// tile, its first COLS / 4 lanes four columns each, so that the row address is
-// scalar and the column arithmetic is done once.  Loads read 16 bytes from
-// addresses clamped into the image (all are in flight together); values outside
-// it become 0 when stored.
-template <class C>
-struct CellTile {
-  using F = typename C::F;
-  struct __attribute__((packed, aligned(4))) Quad { float v[4]; };
-  static constexpr int NR = (C::ROWS + C::NW - 1) / C::NW;   // rows per wave
-  static constexpr int PLANE = C::ROWS * C::PITCH;
-  static_assert(C::COLS % 4 == 0 && C::COLS <= 256, "four columns per lane");
-  int H, W, r0, w;
-  int gx;       // image column of this lane's first value
-  bool inner;   // every column of the tile is inside the image (uniform)
-  f32x4 v[NR];
-  __device__ CellTile(int H_, int W_, int k0, int l0, int w_)
-      : H(H_), W(W_), r0(k0 - CELL_OFF), w(w_),
-        gx(l0 - CELL_OFF + 4 * min((int)(threadIdx.x & 63), C::COLS / 4 - 1)),
-        inner(l0 - CELL_OFF >= 0 && l0 - CELL_OFF + C::COLS <= W_) {}
-  // first column read: the four columns from gx, moved inside an image of at least
-  // four columns
-  __device__ int first(int g) const { return min(max(g, 0), max(W - 4, 0)); }
-  __device__ void load(const float* __restrict__ src) {
-    int g = gx;
-    __asm__ volatile("" : "+v"(g));   // keep the address arithmetic here
-    const int c = first(g);
-    if (W >= 4) {
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const int gy = min(max(r0 + w + C::NW * i, 0), H - 1);
-        const Quad q = *reinterpret_cast<const Quad*>(src + (int64_t)gy * W + c);
-        v[i] = f32x4{q.v[0], q.v[1], q.v[2], q.v[3]};
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const float* rp = src + (int64_t)min(max(r0 + w + C::NW * i, 0), H - 1) * W;
-        v[i] = f32x4{rp[0], rp[min(1, W - 1)], rp[min(2, W - 1)], 0.f};
-      }
-    }
-  }
-  __device__ void store(unsigned short* sh) {
-    int g = gx;
-    __asm__ volatile("" : "+v"(g));
-    if (!inner) {
-      // move each value to its column, 0 outside the image
-      const int d = g - first(g);
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const f32x4 o = v[i];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          const int at = x + d;
-          const float val = at <= 0 ? o[0] : at == 1 ? o[1] : at == 2 ? o[2] : o[3];
-          v[i][x] = (g + x >= 0 && g + x < W) ? val : 0.f;
-        }
-      }
-    }
-    if ((int)(threadIdx.x & 63) >= C::COLS / 4) return;
-    unsigned short* dst = sh + w * C::PITCH + 4 * (threadIdx.x & 63);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int row = w + C::NW * i, gy = r0 + row;
-      if ((i + 1) * C::NW > C::ROWS && row >= C::ROWS) break;
-      const bool iny = gy >= 0 && gy < H;
-      uint32_t a[F::NB], b[F::NB];
-      cell_split2<F::PREC>(iny ? f32x2{v[i][0], v[i][1]} : f32x2{0.f, 0.f}, a);
-      cell_split2<F::PREC>(iny ? f32x2{v[i][2], v[i][3]} : f32x2{0.f, 0.f}, b);
-#pragma unroll
-      for (int p = 0; p < F::NA; ++p)
-        *reinterpret_cast<uint2*>(dst + p * PLANE + C::NW * i * C::PITCH) = make_uint2(a[p], b[p]);
-    }
-  }
-};
-
 // The forward's weights of this lane's outputs, loaded while the last class of
 // the frame runs, so that the epilogue does not wait for HBM.
 template <class C>
@@ -262,58 +134,6 @@ __device__ inline void cell_fwd_body(const MfmaLaunch& a, const int tile, const 
   if (a.part != nullptr) {
     const double s = block_sum<C::NT>(llp, red);
     if (threadIdx.x == 0) a.part[(int64_t)group * a.ntiles + tile] = s;
-  }
-}
-
-// Epilogue of the adjoint: Dn = acc; the fused update of Eq. (2) with its FP64
-// change partials, or a store into the partial plane.
-template <class C>
-__device__ inline void cell_adj_epilogue(const MfmaLaunch& a, const f32x4 (&acc)[C::G],
-                                         const CellLane& p, int tile, int group, double* red) {
-  const int64_t N = (int64_t)a.H * a.W;
-  float* plane = a.fused ? nullptr : a.plane + (int64_t)group * N;
-  const bool al = (a.W & 3) == 0 && (a.fused ? aligned16(a.x) && aligned16(a.B) : aligned16(plane));
-  const bool vec = al && p.col + 3 < a.W;
-  double dsq = 0.0, xsq = 0.0;
-  if (!a.fused) {
-#pragma unroll
-    for (int g = 0; g < C::G; ++g) {
-      const int k = p.row0 + 4 * g;
-      const float v[4] = {acc[g][0], acc[g][1], acc[g][2], acc[g][3]};
-      if (k < a.H && p.col < a.W) store4(plane, k, p.col, a.W, vec, v);
-    }
-    return;
-  }
-  float xo[C::G][4], bv[C::G][4];
-#pragma unroll
-  for (int g = 0; g < C::G; ++g) {
-    load4(a.x, p.row0 + 4 * g, p.col, a.H, a.W, vec, xo[g]);
-    load4(a.B, p.row0 + 4 * g, p.col, a.H, a.W, vec, bv[g]);
-  }
-#pragma unroll
-  for (int g = 0; g < C::G; ++g) {
-    const int k = p.row0 + 4 * g;
-    if (k >= a.H || p.col >= a.W) continue;
-    float xn[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      xn[i] = em_update_value(xo[g][i], bv[g][i], acc[g][i]);
-      if (p.col + i < a.W) {
-        const double d = (double)xn[i] - (double)xo[g][i];
-        dsq += d * d;
-        xsq += (double)xo[g][i] * (double)xo[g][i];
-      }
-    }
-    store4(a.x, k, p.col, a.W, vec, xn);
-  }
-  if (a.part != nullptr) {
-    const double s1 = block_sum<C::NT>(dsq, red);
-    __syncthreads();
-    const double s2 = block_sum<C::NT>(xsq, red + C::NW);
-    if (threadIdx.x == 0) {
-      a.part[2 * tile] = s1;
-      a.part[2 * tile + 1] = s2;
-    }
   }
 }
 

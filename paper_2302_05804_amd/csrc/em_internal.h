@@ -219,6 +219,18 @@ size_t cell_table_bytes(int precision, int n);
 hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s);
 hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, const int4* items,
                                int n_items, int grid, hipStream_t s, bool robust);
+// sr = 2, FP32 (em_cell2.hip)
+inline bool uses_cell2(const Geometry& g) { return g.sr == 2 && g.mc32 != 0; }
+int cell2_fwd_tile_h();   // frame pixels
+int cell2_fwd_tile_w();
+int cell2_adj_tile_h();   // latent pixels
+int cell2_adj_tile_w();
+size_t cell2_table_bytes(int n, int dir);
+hipError_t launch_cell2_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
+                               hipStream_t s);
+bool cell2_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaLaunch& a);
+hipError_t launch_cell2(const Geometry& g, int dir, int tiles, int groups, const MfmaLaunch& a,
+                        hipStream_t s);
 hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               bool lo_band, hipStream_t s);
 // sr = 2 matrix-core kernels (em_mfma2.hip); K <= 43 padded to 43

@@ -860,6 +860,7 @@ int mfma_table_rows(int KT) { return 16 * ((KT + 15) / 16); }
 
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band) {
+  if (uses_cell2(g)) return launch_cell2_tables(g, psf, tab_fwd, tab_adj, s);
   if (g.sr == 2) return launch_mfma2_tables(g, psf, tab_fwd, tab_adj, s);
   if (uses_cell(g)) return launch_cell_tables(g, psf, tab_fwd, tab_adj, lo_band, s);
   const int KTP = mfma_table_rows(g.KT);
@@ -882,6 +883,7 @@ int mfma_tile_h(const Geometry& g) {
 int mfma_tile_w(const Geometry& g) { return g.small16 ? MF_SMALL : MF_TILE; }
 
 size_t mfma_table_bytes(const Geometry& g, int dir) {
+  if (uses_cell2(g)) return cell2_table_bytes(g.n, dir);
   if (g.sr == 2) return dir == 0 && uses_m2n(g) ? mfma2n_table_bytes(g.n) : mfma2_table_bytes(g.n, dir);
   if (g.mc32) return cell_table_bytes(g.precision, g.n);
   // fragments, then one scale exponent per frame
@@ -1044,6 +1046,7 @@ bool mfma_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaL
        a.s16 != (int64_t)r16_rows(g) * r16_pitch(g) || a.out_y != nullptr || a.out != nullptr ||
        (dir == 1 && a.in != nullptr)))
     return false;
+  if (uses_cell2(g)) return cell2_desc_ok(g, dir, tiles, groups, a);
   if (g.sr == 2) return mfma2_desc_ok(g, dir, tiles, groups, a);
   return a.H == g.Hl && a.W == g.Wl &&
          launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g), mfma_tile_w(g));
@@ -1251,6 +1254,7 @@ hipError_t launch_r16_scale(const Geometry& g, const float* x, float* xpart, con
 
 hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int groups,
                        const MfmaLaunch& a, hipStream_t s) {
+  if (uses_cell2(g)) return launch_cell2(g, dir, tiles, groups, a, s);
   if (g.sr == 2) return launch_mfma2(g, dir, variant, tiles, groups, a, s);
   if (!mfma_desc_ok(g, dir, tiles, groups, a)) return hipErrorInvalidValue;
   dim3 grid(tiles, groups);

@@ -78,3 +78,29 @@ def test_fp32_large_and_small_values():
     mo = oracle.forward(psf[0], x, 1)
     assert np.isfinite(m).all()
     assert np.abs(m / mo - 1).max() <= FP32_BOUND
+
+
+@pytest.mark.parametrize("hf,wf,n", [
+    (64, 64, 4),       # one adjoint tile down, whole four-frame products
+    (65, 131, 5),      # one row and column into the next tiles, three frames of a product empty
+    (33, 130, 1), (8192, 1, 2), (2100, 2, 3),
+])
+def test_fp32_sr2_operators_at_tile_edges(hf, wf, n):
+    em = _em()
+    K = 43
+    rng = np.random.default_rng(hf * 7 + wf)
+    psf = rng.uniform(0, 1, (n, K, K)).astype(np.float32)
+    psf /= psf.sum(axis=(1, 2), keepdims=True)
+    x = np.exp(rng.uniform(np.log(1e-2), np.log(1e5), (2 * hf, 2 * wf))).astype(np.float32)
+    r = rng.normal(0, 1, (n, hf, wf)).astype(np.float32)
+    p = em.Problem.make(n, hf, wf, K, sr=2)
+    m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy().astype(np.float64)
+    s = em.adjoint_op(p, to_dev(psf), to_dev(r)).cpu().numpy().astype(np.float64)
+    # one more rounding: the taps of the box-extended kernel
+    bound = FP32_BOUND + 2.0 ** -24
+    for t in range(n):
+        mo, so = oracle.forward(psf[t], x, 2), oracle.adjoint(psf[t], r[t], 2)
+        sa = oracle.adjoint(psf[t], np.abs(r[t]), 2)
+        ef, ea = np.abs(m[t] - mo) / mo, np.abs(s[t] - so) / sa
+        log(f"sr=2 {hf}x{wf} frame {t}: forward {ef.max():.2e}, adjoint {ea.max():.2e} of the absolute sums")
+        assert ef.max() <= bound and ea.max() <= bound
