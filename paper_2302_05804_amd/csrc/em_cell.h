@@ -343,6 +343,33 @@ __device__ __attribute__((always_inline)) inline void cell_frame(
   cell_class<C, 3>(im + 3 * C::PITCH, it + 3 * C::PITCH, plane, T, acc, hook);
 }
 
+// Which fragment of unit u of a class stands in position `frag` (part < 0: none).
+struct CellFragId {
+  int part, j;
+  bool tail;
+};
+template <class F>
+__device__ inline CellFragId cell_frag_id(int u, int frag) {
+  CellFragId id{-1, 0, false};
+  for (int p = 0; p < F::NB; ++p)
+    for (int j = u * F::JU; j < (u + 1) * F::JU; ++j) {
+      if (F::has_main(p, j) && F::slot(p, j, false) == frag) id = {p, j, false};
+      if (F::has_tail(p, j) && F::slot(p, j, true) == frag) id = {p, j, true};
+    }
+  return id;
+}
+
+// Part `part` of one value (0 where there is none).
+template <int PREC>
+__device__ inline unsigned short cell_part(float v, int part) {
+  uint32_t q[Prec<PREC>::NB];
+  cell_split2<PREC>(f32x2{v, 0.f}, q);
+  uint32_t out = 0;
+#pragma unroll
+  for (int x = 0; x < Prec<PREC>::NB; ++x) out = x == part ? q[x] : out;
+  return (unsigned short)out;
+}
+
 // Position of this lane: cell row pr of its outputs, its cell's first column.
 struct CellLane {
   int row0, col;   // image row of group 0's outputs of this lane, first of 4 columns

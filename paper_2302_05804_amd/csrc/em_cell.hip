@@ -224,43 +224,38 @@ __global__ __launch_bounds__(C::NT) void cell_batched(const MfmaLaunch* __restri
   }
 }
 
-// Table of one frame (blockIdx.x), one unit per blockIdx.y: lane (m, gq) of a
-// fragment holds T[m][window row, column 8 gq + e] of its part (see em_cell.h);
-// dir 0: g = f flipped (forward), dir 1: g = f; f zero-padded from K to 43.
+// Tables of one frame (blockIdx.x), one unit per blockIdx.y, both directions and four
+// fragments to a block in blockIdx.z (with one block per unit and direction the 12
+// frames of a 700 x 800 job took 28 us in FP32, 64 us in the banded form): lane
+// (m, gq) of a fragment holds T[m][window row, column 8 gq + e] of its part (see
+// em_cell.h); direction 0: g = f flipped (forward), 1: g = f; f zero-padded from K
+// to 43.
 template <class F>
-__global__ __launch_bounds__(256) void cell_table_kernel(const float* psf, int K, int dir,
-                                                         unsigned short* tab) {
+__global__ __launch_bounds__(256) void cell_table_kernel(const float* psf, int K,
+                                                         unsigned short* tab_fwd,
+                                                         unsigned short* tab_adj) {
   const int t = blockIdx.x, unit = blockIdx.y, E = unit / F::NU, u = unit % F::NU;
+  const int dir = blockIdx.z & 1, frag = 4 * (blockIdx.z >> 1) + (threadIdx.x >> 6);
+  if (frag >= F::NFU) return;
+  unsigned short* tab = dir == 0 ? tab_fwd : tab_adj;
   const int off = (CELL_K - K) / 2;
   const float* f = psf + (int64_t)t * K * K;
-  for (int i = threadIdx.x; i < F::NFU * 64; i += 256) {
-    const int lane = i & 63, m = lane & 15, gq = lane >> 4;
-    int part = -1, j = 0;
-    bool tail = false;
-    for (int p = 0; p < F::NB; ++p)
-      for (int jj = u * F::JU; jj < (u + 1) * F::JU; ++jj) {
-        if (F::has_main(p, jj) && F::slot(p, jj, false) == i >> 6) { part = p; j = jj; tail = false; }
-        if (F::has_tail(p, jj) && F::slot(p, jj, true) == i >> 6) { part = p; j = jj; tail = true; }
-      }
-    unsigned short* dst = tab + (((int64_t)t * F::UPF + unit) * F::NFU * 64 + i) * 8;
-    for (int e = 0; e < 8; ++e) {
-      // window row and column of this K position
-      const int d = 4 * (j + (tail ? gq >> 1 : 0)) + E;
-      const int k = tail ? 32 + 8 * (gq & 1) + e : 8 * gq + e;
-      const int ta = d - 1 - (m >> 2), tb = k - 1 - (m & 3);
-      float gv = 0.f;
-      if (part >= 0 && ta >= 0 && ta < CELL_K && tb >= 0 && tb < CELL_K &&
-          (part == 0 || !F::BAND || (ta >= 11 && ta <= 31))) {
-        const int fa = (dir == 0 ? CELL_K - 1 - ta : ta) - off;
-        const int fb = (dir == 0 ? CELL_K - 1 - tb : tb) - off;
-        if (fa >= 0 && fa < K && fb >= 0 && fb < K) gv = f[fa * K + fb];
-      }
-      uint32_t q[F::NB];
-      cell_split2<F::PREC>(f32x2{gv, 0.f}, q);
-      uint32_t out = 0;
-      for (int x = 0; x < F::NB; ++x) out = x == part ? q[x] : out;
-      dst[e] = (unsigned short)out;
+  const int lane = threadIdx.x & 63, m = lane & 15, gq = lane >> 4;
+  const CellFragId id = cell_frag_id<F>(u, frag);
+  unsigned short* dst = tab + ((((int64_t)t * F::UPF + unit) * F::NFU + frag) * 64 + lane) * 8;
+  for (int e = 0; e < 8; ++e) {
+    // window row and column of this K position
+    const int d = 4 * (id.j + (id.tail ? gq >> 1 : 0)) + E;
+    const int k = id.tail ? 32 + 8 * (gq & 1) + e : 8 * gq + e;
+    const int ta = d - 1 - (m >> 2), tb = k - 1 - (m & 3);
+    float gv = 0.f;
+    if (id.part >= 0 && ta >= 0 && ta < CELL_K && tb >= 0 && tb < CELL_K &&
+        (id.part == 0 || !F::BAND || (ta >= 11 && ta <= 31))) {
+      const int fa = (dir == 0 ? CELL_K - 1 - ta : ta) - off;
+      const int fb = (dir == 0 ? CELL_K - 1 - tb : tb) - off;
+      if (fa >= 0 && fa < K && fb >= 0 && fb < K) gv = f[fa * K + fb];
     }
+    dst[e] = cell_part<F::PREC>(gv, id.part);
   }
 }
 
@@ -326,17 +321,15 @@ hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, 
 
 hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               bool lo_band, hipStream_t s) {
-  for (int dir = 0; dir < 2; ++dir) {
-    unsigned short* t = static_cast<unsigned short*>(dir == 0 ? tab_fwd : tab_adj);
-    auto go = [&](auto form) {
-      using F = decltype(form);
-      hipLaunchKernelGGL(cell_table_kernel<F>, dim3(g.n, F::UPF), dim3(256), 0, s, psf, g.K, dir, t);
-    };
-    if (g.precision == EM_FP32) go(CellForm<EM_FP32, false>{});
-    else if (g.precision == EM_BF16) go(CellForm<EM_BF16, false>{});
-    else if (lo_band) go(CellForm<EM_BF16_SPLIT, true>{});
-    else go(CellForm<EM_BF16_SPLIT, false>{});
-  }
+  auto go = [&](auto form) {
+    using F = decltype(form);
+    hipLaunchKernelGGL(cell_table_kernel<F>, dim3(g.n, F::UPF, 2 * ((F::NFU + 3) / 4)), dim3(256), 0, s, psf,
+                       g.K, static_cast<unsigned short*>(tab_fwd), static_cast<unsigned short*>(tab_adj));
+  };
+  if (g.precision == EM_FP32) go(CellForm<EM_FP32, false>{});
+  else if (g.precision == EM_BF16) go(CellForm<EM_BF16, false>{});
+  else if (lo_band) go(CellForm<EM_BF16_SPLIT, true>{});
+  else go(CellForm<EM_BF16_SPLIT, false>{});
   return hipGetLastError();
 }
 

@@ -180,36 +180,27 @@ __device__ inline void cell2_fwd_body(const MfmaLaunch& a, const int tile, const
   }
 }
 
-// Forward table of four frames (blockIdx.x), one unit per blockIdx.y.
+// Forward table of four frames (blockIdx.x), one unit per blockIdx.y, four fragments
+// per blockIdx.z.
 template <class F>
 __global__ __launch_bounds__(256) void cell2_fwd_table_kernel(const float* psf, int n, int K,
                                                               unsigned short* tab) {
   const int unit = blockIdx.y, E = unit / F::NU, u = unit % F::NU;
-  for (int i = threadIdx.x; i < F::NFU * 64; i += 256) {
-    const int lane = i & 63, m = lane & 15, gq = lane >> 4;
-    int part = -1, j = 0;
-    bool tail = false;
-    for (int p = 0; p < F::NB; ++p)
-      for (int jj = u * F::JU; jj < (u + 1) * F::JU; ++jj) {
-        if (F::has_main(p, jj) && F::slot(p, jj, false) == i >> 6) { part = p; j = jj; tail = false; }
-        if (F::has_tail(p, jj) && F::slot(p, jj, true) == i >> 6) { part = p; j = jj; tail = true; }
-      }
-    const int t = CELL2_FQ * blockIdx.x + (m >> 2);
-    const float* h = psf + (int64_t)min(t, n - 1) * K * K;
-    unsigned short* dst = tab + (((int64_t)blockIdx.x * F::UPF + unit) * F::NFU * 64 + i) * 8;
-    for (int e = 0; e < 8; ++e) {
-      const int d = 4 * (j + (tail ? gq >> 1 : 0)) + E;
-      const int k = tail ? 32 + 8 * (gq & 1) + e : 8 * gq + e;
-      const int ta = d - 1 - 2 * ((m >> 1) & 1), tb = k - 1 - 2 * (m & 1);
-      float gv = 0.f;
-      if (part >= 0 && t < n && ta >= 0 && ta < CELL2_KC && tb >= 0 && tb < CELL2_KC)
-        gv = box_kernel(h, K, CELL2_KC - 1 - ta, CELL2_KC - 1 - tb);
-      uint32_t q[F::NB];
-      cell_split2<F::PREC>(f32x2{gv, 0.f}, q);
-      uint32_t out = 0;
-      for (int x = 0; x < F::NB; ++x) out = x == part ? q[x] : out;
-      dst[e] = (unsigned short)out;
-    }
+  const int frag = 4 * blockIdx.z + (threadIdx.x >> 6);
+  if (frag >= F::NFU) return;
+  const int lane = threadIdx.x & 63, m = lane & 15, gq = lane >> 4;
+  const CellFragId id = cell_frag_id<F>(u, frag);
+  const int t = CELL2_FQ * blockIdx.x + (m >> 2);
+  const float* h = psf + (int64_t)min(t, n - 1) * K * K;
+  unsigned short* dst = tab + ((((int64_t)blockIdx.x * F::UPF + unit) * F::NFU + frag) * 64 + lane) * 8;
+  for (int e = 0; e < 8; ++e) {
+    const int d = 4 * (id.j + (id.tail ? gq >> 1 : 0)) + E;
+    const int k = id.tail ? 32 + 8 * (gq & 1) + e : 8 * gq + e;
+    const int ta = d - 1 - 2 * ((m >> 1) & 1), tb = k - 1 - 2 * (m & 1);
+    float gv = 0.f;
+    if (id.part >= 0 && t < n && ta >= 0 && ta < CELL2_KC && tb >= 0 && tb < CELL2_KC)
+      gv = box_kernel(h, K, CELL2_KC - 1 - ta, CELL2_KC - 1 - tb);
+    dst[e] = cell_part<F::PREC>(gv, id.part);
   }
 }
 
@@ -390,26 +381,23 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
   cell_adj_epilogue<C>(a, acc, p, tile, group, red);
 }
 
+// Adjoint table of one frame (blockIdx.x), one class per blockIdx.y, four fragments per
+// blockIdx.z.
 template <class C>
 __global__ __launch_bounds__(256) void cell2_adj_table_kernel(const float* psf, int K,
                                                               unsigned short* tab) {
-  const int t = blockIdx.x, E = blockIdx.y;
+  const int t = blockIdx.x, E = blockIdx.y, f = 4 * blockIdx.z + (threadIdx.x >> 6);
+  if (f >= C::NF) return;
   const float* h = psf + (int64_t)t * K * K;
-  for (int i = threadIdx.x; i < C::NF * 64; i += 256) {
-    const int lane = i & 63, m = lane & 15, x = lane >> 4;
-    const int f = i >> 6, part = f / 9, u = f % 9 / 3, P = f % 3;
-    const int o = 4 * P + x, d = 2 * (4 * u + o / 3) + E;
-    unsigned short* dst = tab + (((int64_t)t * 2 + E) * C::NF * 64 + i) * 8;
-    for (int e = 0; e < 8; ++e) {
-      const int ka = 2 * d - (m >> 2), kb = 2 * (8 * (o % 3) + e) - (m & 3);
-      float gv = 0.f;
-      if (ka >= 0 && ka < CELL2_KC && kb >= 0 && kb < CELL2_KC) gv = box_kernel(h, K, ka, kb);
-      uint32_t q[C::NB];
-      cell_split2<C::PREC>(f32x2{gv, 0.f}, q);
-      uint32_t out = 0;
-      for (int y = 0; y < C::NB; ++y) out = y == part ? q[y] : out;
-      dst[e] = (unsigned short)out;
-    }
+  const int lane = threadIdx.x & 63, m = lane & 15, x = lane >> 4;
+  const int part = f / 9, u = f % 9 / 3, P = f % 3;
+  const int o = 4 * P + x, d = 2 * (4 * u + o / 3) + E;
+  unsigned short* dst = tab + ((((int64_t)t * 2 + E) * C::NF + f) * 64 + lane) * 8;
+  for (int e = 0; e < 8; ++e) {
+    const int ka = 2 * d - (m >> 2), kb = 2 * (8 * (o % 3) + e) - (m & 3);
+    float gv = 0.f;
+    if (ka >= 0 && ka < CELL2_KC && kb >= 0 && kb < CELL2_KC) gv = box_kernel(h, K, ka, kb);
+    dst[e] = cell_part<C::PREC>(gv, part);
   }
 }
 
@@ -439,9 +427,9 @@ size_t cell2_table_bytes(int n, int dir) {
 
 hipError_t launch_cell2_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                                hipStream_t s) {
-  hipLaunchKernelGGL(cell2_fwd_table_kernel<Fwd2::F>, dim3((g.n + CELL2_FQ - 1) / CELL2_FQ, Fwd2::F::UPF),
+  hipLaunchKernelGGL(cell2_fwd_table_kernel<Fwd2::F>, dim3((g.n + CELL2_FQ - 1) / CELL2_FQ, Fwd2::F::UPF, (Fwd2::F::NFU + 3) / 4),
                      dim3(256), 0, s, psf, g.n, g.K, static_cast<unsigned short*>(tab_fwd));
-  hipLaunchKernelGGL(cell2_adj_table_kernel<Adj2>, dim3(g.n, 2), dim3(256), 0, s, psf, g.K,
+  hipLaunchKernelGGL(cell2_adj_table_kernel<Adj2>, dim3(g.n, 2, (Adj2::NF + 3) / 4), dim3(256), 0, s, psf, g.K,
                      static_cast<unsigned short*>(tab_adj));
   return hipGetLastError();
 }
