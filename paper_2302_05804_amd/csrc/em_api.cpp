@@ -98,13 +98,16 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
 
 // Frame groups of a cell kernel launch (one workgroup fills a compute unit): the
 // count whose rounds over the 256 compute units, times a workgroup's frames plus
-// `fixed` (its set-up, in frames), take the least time.
-static int cell_groups(int tiles, int n, double fixed, int most) {
+// `fixed` (its set-up, in frames), take the least time.  `plane`: what writing and
+// reading one tile of a partial plane takes, in frames times compute units (none
+// with one group).
+static int cell_groups(int tiles, int n, double fixed, double plane, int most) {
   int best = 1;
   double cost = 1e300;
   for (int g = 1; g <= std::min(n, most); ++g) {
     const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
-    const double c = (double)cdiv((int64_t)tiles * groups, 256) * ((double)fpg + fixed);
+    const double c = (double)cdiv((int64_t)tiles * groups, 256) * ((double)fpg + fixed) +
+                     (groups > 1 ? plane * (double)groups * tiles : 0.0);
     if (c < 0.98 * cost) {
       cost = c;
       best = (int)groups;
@@ -138,10 +141,10 @@ Plan make_plan(const Geometry& g) {
   int fg = (int)std::min<int64_t>(g.n, cdiv(target, large ? large : pl.fwd_tiles));
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
-  if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, g.n));
+  if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, 0.0, g.n));
   if (uses_cell2(g)) {   // four frames to a product
     const int quads = (int)cdiv(g.n, 4);
-    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, quads));
+    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, 0.0, quads));
   }
   if (uses_m2n(g)) pl.fwd_fpg = M2N_FPG;   // the frames are the products' N dimension
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
@@ -166,10 +169,14 @@ Plan make_plan(const Geometry& g) {
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
   }
   if (uses_cell(g) || uses_cell2(g)) {
-    // never more partial planes than the rule above holds, which the split forms'
-    // workspaces have always had
-    const int most = g.mc32 ? std::min(g.n, 16) : pl.adj_groups;
-    pl.adj_fpg = (int)cdiv(g.n, cell_groups(pl.adj_tiles, g.n, 0.3, most));
+    // the split forms take more partial planes than the rule above only where u and r
+    // alone are beyond em_run_noalloc's scratch, so that it takes what it always took
+    const bool large_job = (int64_t)g.n * g.Nf * 8 > (int64_t)EM_NOALLOC_SCRATCH_BYTES;
+    const int most = g.mc32 || large_job ? std::min(g.n, 16) : pl.adj_groups;
+    // 8 bytes per pixel of a tile at 4 TB/s against a frame's products of a tile:
+    // 128 x 128 in 18 us (BF16 split), 64 x 128 in 27 us (FP32), in 7 us for sr = 2
+    const double plane = g.sr == 2 ? 0.0024 : g.mc32 ? 0.0006 : 0.0018;
+    pl.adj_fpg = (int)cdiv(g.n, cell_groups(pl.adj_tiles, g.n, 0.3, plane, most));
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
   }
   if (g.weight_mode == EM_W_LITERAL) {
