@@ -47,6 +47,56 @@ int fail(int code, const char* fmt, ...) {
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Frame groups of a launch that has `slots` workgroups resident: the count whose
+// rounds over them, times a workgroup's frames plus `fixed` (its set-up, in frames),
+// take the least time.  `plane`: what writing and reading one tile of a partial plane
+// takes, in frames times compute units (none with one group).
+static int cell_groups(int tiles, int n, double fixed, double plane, int most, int slots = 256,
+                       double* least = nullptr) {
+  int best = 1;
+  double cost = 1e300;
+  for (int g = 1; g <= std::min(n, most); ++g) {
+    const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
+    const double c = (double)cdiv((int64_t)tiles * groups, slots) * ((double)fpg + fixed) +
+                     (groups > 1 ? plane * (double)groups * tiles : 0.0);
+    if (c < 0.98 * cost) {
+      cost = c;
+      best = (int)groups;
+    }
+  }
+  if (least) *least = cost;
+  return best;
+}
+
+// Frame groups of the adjoint of a matrix-core job of `tiles` tiles (their number
+// fixes the order of the frame sum).
+static int adjoint_groups(int tiles, int n) {
+  if (tiles >= 128) return 1;
+  const int64_t fpg = cdiv(n, std::max<int64_t>(1, std::min<int64_t>(n, cdiv(512, tiles))));
+  return (int)cdiv(n, fpg);
+}
+
+// FP16 split, sr = 1: tiles of 128 x 128 outputs (one workgroup to a compute unit) or
+// of 64 x 64 (two).  Forward (its groups are free): a frame takes 27 us in a large
+// tile and 17.5 us in each of two small ones; small ones from a gain of 7 % on (us,
+// large / small: 25 x 500 x 400 64 / 57, 6 x 900 x 700 61 / 41, 33 x 400 x 500 86 / 71;
+// 16 x 640^2 63 / 75, 20 x 1000 x 300 65 / 80, 10 x 1024^2 90 / 93).  Adjoint (its
+// groups are those of the large tiles): a small tile is a quarter of the work at 1 / f
+// of the efficiency, f = 1.4 on binary16 r planes (12 x 1500 x 1777, 168 large tiles:
+// 282 against 311 us; 33 x 1999 x 2111, 272: 1396 against 1186 us), 1.8 where it
+// stages FP32 r (342 against 499 us).
+static constexpr int SMALL16_SLOTS = 512;
+static int small_tiles16(const Geometry& g) {
+  const int big = (int)(cdiv(g.Hf, 128) * cdiv(g.Wf, 128)), small = (int)(cdiv(g.Hf, 64) * cdiv(g.Wf, 64));
+  double cb, cs;
+  (void)cell_groups(big, g.n, 0.3, 0.0, g.n, 256, &cb);
+  (void)cell_groups(small, g.n, 0.3, 0.0, g.n, SMALL16_SLOTS, &cs);
+  const int64_t G = adjoint_groups(big, g.n);
+  const double f = g.weight_mode == EM_W_ADJOINT ? 1.4 : 1.8;
+  return (cs * 0.7 < cb ? SMALL16_FWD : 0) |
+         ((double)cdiv(small * G, 256) * 0.25 * f < (double)cdiv(big * G, 256) ? SMALL16_ADJ : 0);
+}
+
 bool make_geometry(const void* problem, Geometry* g, const char** why) {
   const em_problem* p = static_cast<const em_problem*>(problem);
   if (!p) { *why = "problem is NULL"; return false; }
@@ -85,10 +135,8 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   // FP32 on the matrix cores: from 128 x 128 latent pixels on (below, the tables of
   // a frame, 432 KB for sr = 1 and 108 KB for sr = 2, would be most of the workspace)
   g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->Nl >= 128 * 128;
-  // small images in the FP16 split form: up to half the compute units' worth of
-  // 128 x 128 tiles over all frames
-  g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 &&
-               cdiv(g->Hf, 128) * cdiv(g->Wf, 128) * g->n <= 128;
+  g->lean = 0;
+  g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 ? small_tiles16(*g) : 0;
   g->small32 = p->precision == EM_FP32 && !g->mc32 && g->sr == 1 &&
                cdiv(g->Hf, 64) * cdiv(g->Wf, 64) * g->n <= 256;
   if ((int64_t)g->n * g->Nf > ((int64_t)1 << 40)) { *why = "problem too large"; return false; }
@@ -96,24 +144,11 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   return true;
 }
 
-// Frame groups of a cell kernel launch (one workgroup fills a compute unit): the
-// count whose rounds over the 256 compute units, times a workgroup's frames plus
-// `fixed` (its set-up, in frames), take the least time.  `plane`: what writing and
-// reading one tile of a partial plane takes, in frames times compute units (none
-// with one group).
-static int cell_groups(int tiles, int n, double fixed, double plane, int most) {
-  int best = 1;
-  double cost = 1e300;
-  for (int g = 1; g <= std::min(n, most); ++g) {
-    const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
-    const double c = (double)cdiv((int64_t)tiles * groups, 256) * ((double)fpg + fixed) +
-                     (groups > 1 ? plane * (double)groups * tiles : 0.0);
-    if (c < 0.98 * cost) {
-      cost = c;
-      best = (int)groups;
-    }
-  }
-  return best;
+// The smallest workspace: no matrix-core tables of the FP32 form, partial arrays for
+// the large tiles and their groups only.
+static void make_lean(Geometry* g) {
+  g->lean = 1;
+  g->mc32 = g->small16 = 0;
 }
 
 Plan make_plan(const Geometry& g) {
@@ -131,20 +166,27 @@ Plan make_plan(const Geometry& g) {
     pl.fwd_tiles = (int)(cdiv(g.Wf, mfma2_fwd_tile_w(g.precision)) *
                          cdiv(g.Hf, mfma2_fwd_tile_h(g.precision)));
   else if (mf)
-    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w(g)) * cdiv(g.Hf, mfma_tile_h(g)));
+    pl.fwd_tiles = (int)(cdiv(g.Wf, mfma_tile_w(g, 0)) * cdiv(g.Hf, mfma_tile_h(g, 0)));
   else
     pl.fwd_tiles = (int)(cdiv(g.Wf, fwd_tile_w(g)) * cdiv(g.Hf, fwd_tile_h(g)));
+  pl.prep_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(4096, cdiv((int64_t)g.n * g.Nf, 256)));
   // the smaller tiles of small images keep the frame groups of the large ones (and
   // with them the order of the frame sum)
-  const int side = g.small16 ? 128 : 64;
+  const int side = g.small32 ? 64 : 128;
   const int large = g.small16 || g.small32 ? (int)(cdiv(g.Wf, side) * cdiv(g.Hf, side)) : 0;
   int fg = (int)std::min<int64_t>(g.n, cdiv(target, large ? large : pl.fwd_tiles));
   fg = std::max(fg, 1);
   pl.fwd_fpg = (int)cdiv(g.n, fg);
-  if (uses_cell(g)) pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, 0.0, g.n));
+  // the forward's groups do not enter its sums: as many as the loglik partials have
+  // room for (the set-up's, or those of the rule above)
+  const int old = (large ? large : pl.fwd_tiles) * (int)cdiv(g.n, pl.fwd_fpg);
+  const int room = std::max(1, std::max(g.lean ? 0 : pl.prep_blocks, old) / pl.fwd_tiles);
+  if (uses_cell(g) || (g.sr == 1 && g.precision == EM_FP16_SPLIT))
+    pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, 0.0, room,
+                                            g.small16 & SMALL16_FWD ? SMALL16_SLOTS : 256));
   if (uses_cell2(g)) {   // four frames to a product
     const int quads = (int)cdiv(g.n, 4);
-    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, 0.0, quads));
+    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, 0.0, room));
   }
   if (uses_m2n(g)) pl.fwd_fpg = M2N_FPG;   // the frames are the products' N dimension
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
@@ -155,11 +197,14 @@ Plan make_plan(const Geometry& g) {
     pl.adj_tiles = (int)(cdiv(g.Wl, mfma2_adj_tile_w(g.precision)) *
                          cdiv(g.Hl, mfma2_adj_tile_h(g.precision)));
   else if (mf)
-    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w(g)) * cdiv(g.Hl, mfma_tile_h(g)));
+    pl.adj_tiles = (int)(cdiv(g.Wl, mfma_tile_w(g, 1)) * cdiv(g.Hl, mfma_tile_h(g, 1)));
   else
     pl.adj_tiles = (int)(cdiv(g.Wl, adj_tile_w(g)) * cdiv(g.Hl, adj_tile_h(g)));
   const int group_tiles = large ? large : pl.adj_tiles;
-  if (group_tiles >= (mf ? target / 4 : target / 2)) {
+  if (mf) {
+    pl.adj_groups = adjoint_groups(group_tiles, g.n);
+    pl.adj_fpg = (int)cdiv(g.n, pl.adj_groups);
+  } else if (group_tiles >= target / 2) {
     pl.adj_groups = 1;
     pl.adj_fpg = g.n;
   } else {
@@ -172,7 +217,7 @@ Plan make_plan(const Geometry& g) {
     // the split forms take more partial planes than the rule above only where u and r
     // alone are beyond em_run_noalloc's scratch, so that it takes what it always took
     const bool large_job = (int64_t)g.n * g.Nf * 8 > (int64_t)EM_NOALLOC_SCRATCH_BYTES;
-    const int most = g.mc32 || large_job ? std::min(g.n, 16) : pl.adj_groups;
+    const int most = g.mc32 ? g.n : large_job ? std::min(g.n, 16) : pl.adj_groups;
     // 8 bytes per pixel of a tile at 4 TB/s against a frame's products of a tile:
     // 128 x 128 in 18 us (BF16 split), 64 x 128 in 27 us (FP32), in 7 us for sr = 2
     const double plane = g.sr == 2 ? 0.0024 : g.mc32 ? 0.0006 : 0.0018;
@@ -190,7 +235,6 @@ Plan make_plan(const Geometry& g) {
   // em_set_variants on that job change them
   pl.fwd_variant = 0;
   pl.adj_variant = 0;
-  pl.prep_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(4096, cdiv((int64_t)g.n * g.Nf, 256)));
   pl.upd_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(4096, cdiv(g.Nl, 256)));
   pl.max_partials = std::max(pl.fwd_tiles * pl.fwd_groups, std::max(pl.adj_tiles, pl.upd_blocks));
   return pl;
@@ -633,12 +677,12 @@ extern "C" {
 static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float* v,
                      const float* psf, const float* x0, float* x, void* workspace,
                      size_t ws_bytes, void* stream, bool serving, bool check_workspace,
-                     bool allow_mc32 = true) {
+                     bool lean = false) {
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
-  if (serving || !allow_mc32) g.mc32 = 0;
-  if (serving) g.small16 = g.small32 = 0;
+  if (serving) g.mc32 = g.small16 = g.small32 = 0;
+  if (lean) make_lean(&g);
   if (g.weight_mode == EM_W_LITERAL && g.sr != 1)
     return fail(EM_ENOTSUP, "the typeset weighting is defined for sr = 1 only");
   const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
@@ -1261,9 +1305,8 @@ extern "C" int em_run_noalloc(const em_problem* p, const float* y, const float* 
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
   size_t need = make_layout(g, make_plan(g)).total;
-  if (need > EM_NOALLOC_SCRATCH_BYTES && g.mc32) {
-    // without the matrix-core tables of the FP32 form
-    g.mc32 = 0;
+  if (need > EM_NOALLOC_SCRATCH_BYTES) {
+    make_lean(&g);
     need = make_layout(g, make_plan(g)).total;
   }
   if (need > EM_NOALLOC_SCRATCH_BYTES)
@@ -1285,7 +1328,7 @@ extern "C" int em_run_noalloc(const em_problem* p, const float* y, const float* 
   em_ctx c{};
   c.no_graph = true;   // eager launches: nothing is instantiated
   int rc = setup_job(&c, p, y, v, psf, x0, x, g_noalloc_ptr[dev], EM_NOALLOC_SCRATCH_BYTES,
-                     stream, false, false, g.mc32 != 0);
+                     stream, false, false, g.lean != 0);
   if (rc != EM_OK) return rc;
   if ((rc = em_iterate(&c, n_iter, loglik_trace)) != EM_OK) return rc;
   // the next call reuses the array: this one's kernels must be done

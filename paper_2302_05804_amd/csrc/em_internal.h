@@ -43,12 +43,16 @@ enum Scalar {
   S_COUNT = 16
 };
 
+// Geometry::small16
+enum { SMALL16_FWD = 1, SMALL16_ADJ = 2 };
+
 struct Geometry {
   int n, Hf, Wf, sr, Hl, Wl, K, KT, KC;
   int64_t Nf, Nl;
   int precision, weight_mode;
   float nu;   // Student-t degrees of freedom (EM_W_STUDENT_T)
-  // FP16 split form, sr = 1, few 128 x 128 tiles: 64 x 64 outputs per workgroup
+  // FP16 split form, sr = 1: directions (SMALL16_FWD, SMALL16_ADJ) that take 64 x 64
+  // outputs per workgroup instead of 128 x 128
   int small16;
   // FP32 direct convolution, sr = 1, few 64 x 64 tiles: 16 rows per workgroup
   int small32;
@@ -56,6 +60,7 @@ struct Geometry {
   // set by make_geometry where that path is the faster one, cleared where its
   // tables do not fit (serving arenas, the static scratch)
   int mc32;
+  int lean;   // the smallest workspace (em_run_noalloc, where no other fits)
 };
 
 // Launch shape chosen for a geometry (a pure function of the geometry, so the
@@ -267,8 +272,8 @@ hipError_t launch_adjoint_batched(int sr, int KT, const AdjLaunch* descs, const 
 int mfma_variants();
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band = false);
-int mfma_tile_h(const Geometry& g);   // outputs of a workgroup, sr = 1
-int mfma_tile_w(const Geometry& g);
+int mfma_tile_h(const Geometry& g, int dir);   // outputs of a workgroup, sr = 1
+int mfma_tile_w(const Geometry& g, int dir);
 size_t mfma_table_bytes(const Geometry& g, int dir);
 
 // Host-side check that a launch grid matches its descriptor: `tiles` tiles of

@@ -877,10 +877,13 @@ hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd
   return hipGetLastError();
 }
 
-int mfma_tile_h(const Geometry& g) {
-  return uses_cell(g) ? cell_tile_h(g.precision) : g.small16 ? MF_SMALL : MF_TILE;
+static bool small_tile(const Geometry& g, int dir) {
+  return (g.small16 & (dir == 0 ? SMALL16_FWD : SMALL16_ADJ)) != 0;
 }
-int mfma_tile_w(const Geometry& g) { return g.small16 ? MF_SMALL : MF_TILE; }
+int mfma_tile_h(const Geometry& g, int dir) {
+  return uses_cell(g) ? cell_tile_h(g.precision) : small_tile(g, dir) ? MF_SMALL : MF_TILE;
+}
+int mfma_tile_w(const Geometry& g, int dir) { return small_tile(g, dir) ? MF_SMALL : MF_TILE; }
 
 size_t mfma_table_bytes(const Geometry& g, int dir) {
   if (uses_cell2(g)) return cell2_table_bytes(g.n, dir);
@@ -1049,7 +1052,7 @@ bool mfma_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaL
   if (uses_cell2(g)) return cell2_desc_ok(g, dir, tiles, groups, a);
   if (g.sr == 2) return mfma2_desc_ok(g, dir, tiles, groups, a);
   return a.H == g.Hl && a.W == g.Wl &&
-         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g), mfma_tile_w(g));
+         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, mfma_tile_h(g, dir), mfma_tile_w(g, dir));
 }
 
 int r16_pitch(const Geometry& g) {
@@ -1266,7 +1269,7 @@ hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int g
     default: return hipErrorInvalidValue;                                    \
   }
   if (uses_cell(g)) return launch_cell(g.precision, dir, grid, a, s);
-  if (g.small16)
+  if (small_tile(g, dir))
     return g.KT == KT_LARGE ? launch_small<KT_LARGE>(dir, grid, a, s) : launch_small<KT_SMALL>(dir, grid, a, s);
   if (g.KT == KT_LARGE)
     return g.precision == EM_FP16_SPLIT ? launch_dir<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, a, s)
