@@ -80,12 +80,13 @@ def log(msg: str) -> None:
 # The files that hold a form's kernel code; a recorded traffic figure is tied to
 # their contents.
 KERNEL_FILES = {
-    (prec, 1): ["em_mfma.hip", "em_mfma_common.h", "em_device.h"]
-    for prec in ("fp16split", "bf16split", "bf16")
+    ("fp16split", 1): ["em_mfma.hip", "em_mfma_common.h", "em_device.h"],
+    ("fp32", 2): ["em_cell2.hip", "em_cell.h", "em_mfma_common.h", "em_device.h"],
 }
+KERNEL_FILES.update({(prec, 1): ["em_cell.hip", "em_cell.h", "em_mfma_common.h", "em_device.h"]
+                     for prec in ("fp32", "bf16split", "bf16")})
 KERNEL_FILES.update({(prec, 2): ["em_mfma2.hip", "em_mfma2n.hip", "em_mfma_common.h", "em_device.h"]
                      for prec in ("fp16split", "bf16split", "bf16")})
-KERNEL_FILES[("fp32", 1)] = KERNEL_FILES[("fp32", 2)] = ["em_fp32.hip", "em_device.h"]
 
 
 def kernel_sources_sha(prec: str, sr: int = 1) -> str:
@@ -232,7 +233,9 @@ def time_form(em, prob, tensors, prec_name, steps, warmup, stream, nu=0.0, job_i
     # (with the fused update) is the kernel timed on its own
     dom = 1 if nu else (0 if phases[0] >= phases[1] else 1)
     achieved = flops / (phases[dom] / 1e3) / 1e12
-    mf = prec_name != "fp32"
+    # FP32 runs on the matrix cores too (six products of bf16 parts), but for kernels
+    # padded to 15 and latent images below 128 x 128
+    mf = prec_name != "fp32" or (prob.K > 15 and x.numel() >= 128 * 128)
     peak = PEAKS_TFLOPS["bf16" if mf else "fp32"]
     name = ["forward", "adjoint"][dom]
     log(f"  {prec_name}: {gpu_ms / steps:.3f} ms/step (iterations {job_iters - steps + 1}-"

@@ -12,8 +12,7 @@
 //     T[4p + q][d, k] = g[d - 1 - p][k - 1 - q].
 // 43 x 43 of the 46 x 48 window values that can be non-zero are taps: 84%, where a
 // row of 16 outputs (a one-dimensional Toeplitz operand of 43 + 15 values in
-// 64) is 67%: 106 products per 256 outputs and frame in the FP16 split form
-// instead of 128.
+// 64) is 67%.
 //
 // Window row d of cell row R is image row R - 22 + d, and cell rows are 4 apart,
 // so with d = 4 j + E (class E = 0..3, j = 0..11) an image row 4 s + E serves
