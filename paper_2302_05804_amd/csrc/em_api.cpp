@@ -55,7 +55,8 @@ static int cell_groups(int tiles, int n, double fixed, double plane, int most, i
                        double* least = nullptr) {
   int best = 1;
   double cost = 1e300;
-  for (int g = 1; g <= std::min(n, most); ++g) {
+  const int last = std::min(std::min(n, most), 1024);   // beyond, the rounds differ by little
+  for (int g = 1; g <= last; ++g) {
     const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
     const double c = (double)cdiv((int64_t)tiles * groups, slots) * ((double)fpg + fixed) +
                      (groups > 1 ? plane * (double)groups * tiles : 0.0);

@@ -27,7 +27,12 @@
 // in FP32 issues 3.7 PFLOP of products per launch, forward 2.24 ms = 1.64 PFLOP/s,
 // adjoint 2.48 ms (the r tile is staged anew for every frame); the direct FP32
 // convolution took 7.35 and 7.62 ms.  BF16 split on 33 x 1999 x 2111: forward 1.41
-// -> 1.18 ms, adjoint 2.17 -> 1.77 ms against one-dimensional Toeplitz operands.
+// -> 1.18 ms, adjoint 2.17 -> 1.01 ms against one-dimensional Toeplitz operands
+// (alone on the card; 272 tiles in one frame group, two rounds, took 1.77 ms).
+//
+// FP32 parts: a value is hi + mid + lo, each the bf16 nearest to what is left.  All
+// 24 bits are in them from 2^-109 on; below, the last part meets the smallest bf16,
+// 2^-133.  A first part that would round to infinity is clamped.
 //
 // The 48 window columns of a row are one 32-wide chunk ("main") and a 16-wide
 // "tail"; the tails of rows j and j + 1 of a class (image rows 4 s + E and
