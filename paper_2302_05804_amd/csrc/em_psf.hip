@@ -152,8 +152,10 @@ struct PsfDivisor {
   __device__ explicit PsfDivisor(float c_)
       : c(c_), rc(1.f / c_), plain((__float_as_uint(c_) & 0x7fffffu) == 0x7fffffu) {}
   __device__ float divide(float v) const {
-    // quotients and remainders stay normal: below that, divide
-    if (plain || !(fabsf(v) > 1e-30f)) return v / c;
+    // c is in [2^-24, 1]: inside these bounds quotient and remainder are normal and
+    // finite; outside, and for infinities and NaN, divide
+    const float a = fabsf(v);
+    if (plain || !(a > 1e-30f && a < 1e30f)) return v / c;
     const float q = v * rc;
     return fmaf(fmaf(-q, c, v), rc, q);
   }

@@ -183,3 +183,20 @@ def test_paper_super_resolution_pipeline():
     err = rel_l2(xg, xo)
     log(f"  Eq. (4) + up-sampling + Eq. (2): rel L2(x) {err:.2e}")
     assert err <= 1e-4
+
+
+@pytest.mark.parametrize("kf,kh", [(9, 15), (15, 43), (9, 63)])
+@pytest.mark.parametrize("scale", [1e20, 1e30])
+def test_overflowing_second_moments_stop_the_step(kf, kh, scale):
+    """f finite but so large that Adam's second moments overflow: the step divides by
+    an infinite root and is 0, so h keeps its start.  A step length of 0 keeps every
+    other pixel too (0 times a finite quotient)."""
+    import torch
+    em = _em()
+    f = (synth.coarse_psfs(2, kf, 2, seed=kf + kh).astype(np.float64) * scale).astype(np.float32)
+    assert np.isfinite(f).all()
+    h, _ = em.psf_fit(to_dev(f), kh, 2, lr=0.0, steps=5)
+    torch.cuda.synchronize()
+    start = np.stack([oracle.psf_start(f[t], kh, 2) for t in range(2)]).astype(np.float32)
+    log(f"scale {scale:g} Kh={kh}: largest h {h.max():.3e}, start {start.max():.3e}")
+    assert np.array_equal(h.cpu().numpy(), start)
