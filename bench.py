@@ -233,7 +233,7 @@ def time_form(em, prob, tensors, prec_name, steps, warmup, stream, nu=0.0, job_i
     # (with the fused update) is the kernel timed on its own
     dom = 1 if nu else (0 if phases[0] >= phases[1] else 1)
     achieved = flops / (phases[dom] / 1e3) / 1e12
-    # FP32 runs on the matrix cores too (six products of bf16 parts), but for kernels
+    # FP32 runs on the matrix cores too (eight products of bf16 parts), but for kernels
     # padded to 15 and latent images below 128 x 128
     mf = prec_name != "fp32" or (prob.K > 15 and x.numel() >= 128 * 128)
     peak = PEAKS_TFLOPS["bf16" if mf else "fp32"]

@@ -70,11 +70,10 @@ extern "C" {
 #define EM_FP32        0    /* products and sums of binary32 accuracy.
                                15 < K <= 43, 16384 latent pixels and more, not
                                served: on the matrix cores, each operand as
-                               the exact sum of three bf16 parts, six of their
-                               nine products (the others are below 2^-24 of the
-                               whole one), summed in FP32 in levels; measured
-                               error against binary64 is below that of the
-                               direct convolution, which computes all else     */
+                               the exact sum of three bf16 parts, eight of
+                               their nine products (the ninth is below 2^-32 of
+                               the whole one), summed in FP32 in levels.  All
+                               else: direct convolution                        */
 #define EM_BF16_SPLIT  1    /* BF16 MFMA, image and PSF split into hi+lo,
                                three products (hi hi, hi lo, lo hi), FP32
                                accumulation.  K = 43, sr = 1, not served: when

@@ -104,3 +104,30 @@ def test_fp32_sr2_operators_at_tile_edges(hf, wf, n):
         ef, ea = np.abs(m[t] - mo) / mo, np.abs(s[t] - so) / sa
         log(f"sr=2 {hf}x{wf} frame {t}: forward {ef.max():.2e}, adjoint {ea.max():.2e} of the absolute sums")
         assert ef.max() <= bound and ea.max() <= bound
+
+
+@pytest.mark.parametrize("sr", [1, 2])
+def test_fp32_single_products(sr):
+    """One tap: every output is one product (sr = 2: of the adjoint).  FP32 holds it to
+    half a unit, 2^-24; here the sum of the largest part product with the seven
+    others (below 2^-7 of it, seven roundings of 2^-24) rounds once more, and the
+    ninth is below 2^-32: 2^-24 (1 + 2^-3) in all."""
+    em = _em()
+    n, H, W, K = 2, 130 // sr, 260 // sr, 43
+    rng = np.random.default_rng(905 + sr)
+    psf = np.zeros((n, K, K), np.float32)
+    psf[0, 21, 21], psf[1, 3, 40] = rng.uniform(0.1, 1, 2)
+    bound = 2.0 ** -24 * (1 + 2.0 ** -3)
+    p = em.Problem.make(n, H, W, K, sr=sr)
+    r = np.exp(rng.uniform(-5, 5, (n, H, W))).astype(np.float32)
+    s = em.adjoint_op(p, to_dev(psf), to_dev(r)).cpu().numpy().astype(np.float64)
+    pairs = [(s[t], oracle.adjoint(psf[t], r[t], sr)) for t in range(n)]
+    if sr == 1:
+        x = np.exp(rng.uniform(-5, 5, (H, W))).astype(np.float32)
+        m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy().astype(np.float64)
+        pairs += [(m[t], oracle.forward(psf[t], x, 1)) for t in range(n)]
+    for got, want in pairs:
+        at = want > 0
+        err = np.abs(got[at] / want[at] - 1).max()
+        log(f"sr={sr} one tap: largest error {err / 2.0 ** -24:.4f} x 2^-24")
+        assert (got[~at] == 0).all() and err <= bound
