@@ -118,8 +118,8 @@ struct CellForm {
   static constexpr int NA = P::NA, NB = P::NB, NP = P::NP;
   // EM_FP32: sums in levels.  The largest product of each LEVEL rows of a class is
   // summed apart from the other products and from the other rows, then the class,
-  // then the frame, so that the sums round less than the direct convolution's
-  // 43-term chains do
+  // then the frame (adjoint: all frames, in FP64), so that the sums round less than
+  // the direct convolution's 43-term chains do
   static constexpr bool LEVELS = PREC_ == EM_FP32;
   static constexpr int LEVEL = 3;
   // rows per unit (table fragments are staged in LDS one unit at a time, two
@@ -255,13 +255,25 @@ __device__ inline void cell_boundary(CellTab<typename C::F>& T, int boundary, Ho
   hook.after(boundary);
 }
 
+// Where a frame's classes are added up.  FP32: the adjoint adds them to the sum over its
+// frames, in FP64 (in FP32 the sum of 15 frames of 942 x 2100 latent pixels, one
+// group, took x after two iterations from 1.14e-7, with groups of three frames in the
+// direct convolution, to 1.44e-7).
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+__device__ EM_INLINE inline void cell_add(f32x4& sum, const f32x4& v) { sum += v; }
+__device__ EM_INLINE inline void cell_add(f64x4& sum, const f32x4& v) {
+  sum += __builtin_convertvector(v, f64x4);
+}
+template <bool LEVELS>
+using CellSum = std::conditional_t<LEVELS, f64x4, f32x4>;
+
 // One class of one frame.  im, it: this lane's window start in the staged planes
 // for the main and the tail chunk (plane 0, window row E of the wave's first
 // cell row); plane: distance of the planes.
-template <class C, int E, class Hook>
+template <class C, int E, class Sum, class Hook>
 __device__ __attribute__((always_inline)) inline void cell_class(
     const unsigned short* im, const unsigned short* it, int plane, CellTab<typename C::F>& T,
-    f32x4 (&acc)[C::G], Hook& hook) {
+    Sum (&acc)[C::G], Hook& hook) {
   using F = typename C::F;
   using frag = typename C::frag;
   constexpr int G = C::G, NS = G + CELL_NJ - 1;
@@ -320,17 +332,21 @@ __device__ __attribute__((always_inline)) inline void cell_class(
       static_for<G>([&](auto gc) EM_INLINE {
         constexpr int g = G - 1 - gc, j = s - g;
         if constexpr (j >= 0 && j < CELL_NJ) {
-          f32x4& sum = !F::LEVELS ? acc[g] : pa + pb == 0 ? big[F::LEVELS ? g : 0] : small[F::LEVELS ? g : 0];
-          if constexpr (F::mul_main(pa, pb, j) && main_used(pb, j))
-            sum = F::P::mma(Tm[pb][j], Am[s & 1][pa], sum);
-          if constexpr (F::mul_tail(pa, pb, j)) sum = F::P::mma(Tt[pb][j], At[s & 1][pa], sum);
+          auto take = [&](f32x4& sum) EM_INLINE {
+            if constexpr (F::mul_main(pa, pb, j) && main_used(pb, j))
+              sum = F::P::mma(Tm[pb][j], Am[s & 1][pa], sum);
+            if constexpr (F::mul_tail(pa, pb, j)) sum = F::P::mma(Tt[pb][j], At[s & 1][pa], sum);
+          };
+          if constexpr (!F::LEVELS) take(acc[g]);
+          else if constexpr (pa + pb == 0) take(big[g]);
+          else take(small[g]);
         }
       });
     });
   });
   if constexpr (F::LEVELS)
     static_for<G>([&](auto gc) EM_INLINE {
-      acc[gc] += cls[gc] + (big[gc] + small[gc]);
+      cell_add(acc[gc], cls[gc] + (big[gc] + small[gc]));
       // add now: sunk to the frame's end, the addends of every class would be spilled
       __asm__ volatile("" : "+v"(acc[gc]));
     });
@@ -339,10 +355,10 @@ __device__ __attribute__((always_inline)) inline void cell_class(
 // All classes of one frame into acc (one wave's G cell rows x 16 cells).  On
 // entry the frame's first unit is in its slot (a barrier after its copy has
 // been passed) and the second is in flight or landed.
-template <class C, class Hook>
+template <class C, class Sum, class Hook>
 __device__ __attribute__((always_inline)) inline void cell_frame(
     const unsigned short* im, const unsigned short* it, int plane, CellTab<typename C::F>& T,
-    f32x4 (&acc)[C::G], Hook& hook) {
+    Sum (&acc)[C::G], Hook& hook) {
   cell_class<C, 0>(im, it, plane, T, acc, hook);
   cell_class<C, 1>(im + C::PITCH, it + C::PITCH, plane, T, acc, hook);
   cell_class<C, 2>(im + 2 * C::PITCH, it + 2 * C::PITCH, plane, T, acc, hook);

@@ -175,9 +175,10 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
   const CellLane p = cell_lane<C>(k0, l0);
   const unsigned short* im = sh + cell_main_off<C>();
   const unsigned short* it = sh + cell_tail_off<C>();
-  f32x4 acc[C::G];
+  using Sum = CellSum<F::LEVELS>;
+  Sum acc[C::G];
 #pragma unroll
-  for (int g = 0; g < C::G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < C::G; ++g) acc[g] = Sum{0, 0, 0, 0};
   Hook hook{CellTile<C>(a.H, a.W, k0, l0, w), a.in + (int64_t)t0 * N};
   hook.tl.load(hook.next);
   for (int t = t0; t < t1; ++t) {
@@ -185,17 +186,24 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
     cell_wait<0>();
     __syncthreads();
     hook.next = a.in + (int64_t)min(t + 1, t1 - 1) * N;
-    // each frame is summed by itself and then added to the total
-    f32x4 accf[C::G];
+    if constexpr (F::LEVELS) {
+      cell_frame<C>(im, it, PLANE, T, acc, hook);
+    } else {
+      // each frame is summed by itself and then added to the total
+      f32x4 accf[C::G];
 #pragma unroll
-    for (int g = 0; g < C::G; ++g) accf[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    cell_frame<C>(im, it, PLANE, T, accf, hook);
+      for (int g = 0; g < C::G; ++g) accf[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+      cell_frame<C>(im, it, PLANE, T, accf, hook);
 #pragma unroll
-    for (int g = 0; g < C::G; ++g) acc[g] += accf[g];
+      for (int g = 0; g < C::G; ++g) acc[g] += accf[g];
+    }
     __syncthreads();   // every wave is done with the tile
   }
   cell_wait<0>();   // the copies issued past the last unit
-  cell_adj_epilogue<C>(a, acc, p, tile, group, red);
+  f32x4 sum[C::G];
+#pragma unroll
+  for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
+  cell_adj_epilogue<C>(a, sum, p, tile, group, red);
 }
 
 // One job per launch, grid (tiles, frame groups), or the (job, tile, group) items

@@ -215,7 +215,6 @@ struct Adj2Cfg {
   using frag = typename P::frag;
   static constexpr int PREC = PREC_, G = G_, WC = WC_;
   static constexpr int NA = P::NA, NB = P::NB, NP = P::NP;
-  static constexpr bool LEVELS = PREC_ == EM_FP32;
   static constexpr int NW = 4 * WC, NT = 64 * NW;
   static constexpr int TH = 16 * G, TW = 64 * WC;        // latent pixels
   static constexpr int ROWS = TH / 2 + 22, COLS = TW / 2 + 22;   // frame pixels staged
@@ -276,7 +275,7 @@ struct Adj2Tile {
 // One class: `im[P]` this lane's piece of product P at step 0 (window row E).
 template <class C>
 __device__ EM_INLINE inline void cell2_class(const unsigned short* const (&im)[3],
-                                             const typename C::frag* slot, f32x4 (&accf)[C::G]) {
+                                             const typename C::frag* slot, f64x4 (&acc)[C::G]) {
   using frag = typename C::frag;
   constexpr int G = C::G;
   const int lane = threadIdx.x & 63;
@@ -284,9 +283,8 @@ __device__ EM_INLINE inline void cell2_class(const unsigned short* const (&im)[3
   static_for<C::NB>([&](auto pc) EM_INLINE {
     static_for<9>([&](auto fc) EM_INLINE { T[pc][fc] = slot[(pc * 9 + fc) * 64 + lane]; });
   });
-  f32x4 big[C::LEVELS ? G : 1], small[C::LEVELS ? G : 1];
-  if constexpr (C::LEVELS)
-    static_for<G>([&](auto gc) EM_INLINE { big[gc] = small[gc] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+  f32x4 big[G], small[G];
+  static_for<G>([&](auto gc) EM_INLINE { big[gc] = small[gc] = f32x4{0.f, 0.f, 0.f, 0.f}; });
   static_for<G + 2>([&](auto sc) EM_INLINE {
     constexpr int s = sc;
     frag A[C::NA][3];
@@ -300,17 +298,16 @@ __device__ EM_INLINE inline void cell2_class(const unsigned short* const (&im)[3
       static_for<3>([&](auto uc) EM_INLINE {
         constexpr int g = s - uc;
         if constexpr (g >= 0 && g < G) {
-          f32x4& sum = !C::LEVELS ? accf[g] : pa + pb == 0 ? big[C::LEVELS ? g : 0] : small[C::LEVELS ? g : 0];
+          f32x4& sum = pa + pb == 0 ? big[g] : small[g];
           static_for<3>([&](auto Pc) EM_INLINE { sum = C::P::mma(T[pb][3 * uc + Pc], A[pa][Pc], sum); });
         }
       });
     });
   });
-  if constexpr (C::LEVELS)
-    static_for<G>([&](auto gc) EM_INLINE {
-      accf[gc] += big[gc] + small[gc];
-      __asm__ volatile("" : "+v"(accf[gc]));   // add now, as in cell_class
-    });
+  static_for<G>([&](auto gc) EM_INLINE {
+    cell_add(acc[gc], big[gc] + small[gc]);
+    __asm__ volatile("" : "+v"(acc[gc]));   // add now, as in cell_class
+  });
 }
 
 // Adjoint: sum over the frames of this group of F_t^T r_t.  Two r tiles and two
@@ -348,20 +345,17 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
     const int o = 4 * P + (lane >> 4);
     off[P] = 2 * (c + o / 3) * C::PITCH + wc * 32 + 2 * (lane & 15) + 8 * (o % 3);
   }
-  f32x4 acc[C::G];
+  f64x4 acc[C::G];
 #pragma unroll
-  for (int g = 0; g < C::G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < C::G; ++g) acc[g] = f64x4{0., 0., 0., 0.};
   for (int t = t0; t < t1; ++t) {
     const unsigned short* base = sh[(t - t0) & 1];
     const int unit = 2 * (t - t0);
-    f32x4 accf[C::G];
-#pragma unroll
-    for (int g = 0; g < C::G; ++g) accf[g] = f32x4{0.f, 0.f, 0.f, 0.f};
     cell2_issue<C>(tab + (int64_t)(unit + 1) * C::NF * 64, w, slot1);
     tl.template pass<false>(a.in + (int64_t)min(t + 1, t1 - 1) * Nf, H, W, i0, j0, nullptr);
     {
       const unsigned short* const im[3] = {base + off[0], base + off[1], base + off[2]};
-      cell2_class<C>(im, slot0, accf);
+      cell2_class<C>(im, slot0, acc);
     }
     cell_wait<0>();
     __syncthreads();   // slot 1 has landed, slot 0 and the other tile are free
@@ -370,15 +364,16 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
     {
       const unsigned short* const im[3] = {base + C::PITCH + off[0], base + C::PITCH + off[1],
                                            base + C::PITCH + off[2]};
-      cell2_class<C>(im, slot1, accf);
+      cell2_class<C>(im, slot1, acc);
     }
-#pragma unroll
-    for (int g = 0; g < C::G; ++g) acc[g] += accf[g];
     cell_wait<0>();
     __syncthreads();   // the next tile and slot 0 are complete
   }
+  f32x4 sum[C::G];
+#pragma unroll
+  for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
   const CellLane p{k0 + 4 * c + (lane >> 4), l0 + wc * 64 + 4 * (lane & 15)};
-  cell_adj_epilogue<C>(a, acc, p, tile, group, red);
+  cell_adj_epilogue<C>(a, sum, p, tile, group, red);
 }
 
 // Adjoint table of one frame (blockIdx.x), one class per blockIdx.y, four fragments per

@@ -131,3 +131,32 @@ def test_fp32_single_products(sr):
         err = np.abs(got[at] / want[at] - 1).max()
         log(f"sr={sr} one tap: largest error {err / 2.0 ** -24:.4f} x 2^-24")
         assert (got[~at] == 0).all() and err <= bound
+
+
+@pytest.mark.parametrize("sr,hf,wf,n,groups", [
+    (1, 1024, 1024, 8, 2), (1, 940, 2100, 15, 1), (2, 471, 1050, 15, 1), (2, 200, 300, 33, 7),
+])
+def test_fp32_frame_sums(sr, hf, wf, n, groups):
+    """The sum over frames is held in FP64: one tap of 1, unit weights, so that B is
+    the plain sum of the exposures.  The frame groups' sums are rounded once (2^-24 of
+    the total together) and added in FP32 (2^-24 for each further group).  A chain over
+    15 frames in FP32 is off by up to 15 times that."""
+    import torch
+    em = _em()
+    g = torch.Generator(device="cuda").manual_seed(hf + n)
+    y = torch.rand((n, hf, wf), generator=g, device="cuda") + 0.5
+    v = torch.ones_like(y)
+    psf = torch.zeros((n, 43, 43), device="cuda")
+    psf[:, 21, 21] = 1.0
+    p = em.Problem.make(n, hf, wf, 43, sr=sr)
+    x = torch.empty(p.latent_shape, device="cuda")
+    ctx = em.Context(p, y, v, psf, x)
+    B, _ = ctx.terms()
+    ctx.sync()
+    want = y.double().sum(0)
+    if sr == 2:
+        want = want.repeat_interleave(2, 0).repeat_interleave(2, 1)
+    err = float((B.double() / want - 1).abs().max()) / 2.0 ** -24
+    log(f"sr={sr} {n} x {hf} x {wf}: largest error of the frame sum {err:.3f} x 2^-24")
+    ctx.close()
+    assert err <= groups + 0.01
