@@ -392,6 +392,7 @@ static int adjoint_sum(em_ctx* c, const float* in, float* out) {
     m.ntiles = c->pl.adj_tiles;
     m.fused = 0;
     m.lo_band = c->pl.lo_band;
+    m.taps = c->tab;
     EM_HIP(launch_mfma(c->g, 1, c->pl.adj_variant, c->pl.adj_tiles, c->pl.adj_groups, m,
                        c->stream));
   } else {
@@ -431,6 +432,7 @@ void fill_forward_mfma(const em_ctx* c, MfmaLaunch* m, bool write_r, bool loglik
   m->fpg = c->pl.fwd_fpg;
   m->ntiles = c->pl.fwd_tiles;
   m->lo_band = c->pl.lo_band;
+  m->taps = c->tab;
 }
 
 void fill_forward_fp32(const em_ctx* c, FwdLaunch* f, bool write_r, bool loglik) {
@@ -466,6 +468,7 @@ void fill_adjoint_mfma(const em_ctx* c, MfmaLaunch* m, double* part_rc) {
   m->part = fused ? part_rc : nullptr;
   m->plane = c->planes;
   m->lo_band = c->pl.lo_band;
+  m->taps = c->tab;
 }
 
 void fill_adjoint_fp32(const em_ctx* c, AdjLaunch* a, double* part_rc) {
@@ -1142,6 +1145,7 @@ int em_forward_op(const em_problem* p, const float* psf, const float* x, float* 
     mm.W = g.Wf;
     mm.fpg = pl.fwd_fpg;
     mm.ntiles = pl.fwd_tiles;
+    mm.taps = tab;
     EM_HIP(launch_mfma(g, 0, pl.fwd_variant, pl.fwd_tiles, pl.fwd_groups, mm, s));
     return EM_OK;
   }
@@ -1193,6 +1197,7 @@ int em_adjoint_op(const em_problem* p, const float* psf, const float* r, float* 
     mm.fpg = 1;
     mm.ntiles = pl.adj_tiles;
     mm.fused = 0;
+    mm.taps = tab;
     EM_HIP(launch_mfma(g, 1, pl.adj_variant, pl.adj_tiles, g.n, mm, s));
     return EM_OK;
   }

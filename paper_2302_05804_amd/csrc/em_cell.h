@@ -416,6 +416,48 @@ __device__ inline int cell_tail_off() {
          (gq >> 1) * 4 * C::PITCH + 32 + 8 * (gq & 1);
 }
 
+// FP32: an infinity or NaN in an operand does not survive the split into parts (inf -
+// inf) and meets the zeros of the table around the 43 x 43 taps, so it makes NaN of
+// every output whose 46 x 48 window holds it.  The outputs that are not finite are
+// formed once more as the direct convolution does, one at a time: `value(g, i)` for
+// element i of cell row g.  (The BF16 forms leave them: NaN up to three pixels outside
+// the support.  With this step their adjoint spilled: 33 x 1999 x 2111 1.04 -> 1.09 ms.)
+template <int G, class Fn>
+__device__ EM_INLINE inline void cell_repair(f32x4 (&acc)[G], Fn&& value) {
+  uint32_t bad = 0;
+#pragma unroll
+  for (int e = 0; e < 4 * G; ++e)
+    bad |= __builtin_isfinite(acc[e / 4][e % 4]) ? 0u : 1u << e;
+  while (bad != 0) {
+    const int at = __ffs(bad) - 1;
+    bad &= bad - 1;
+    const float v = value(at >> 2, at & 3);
+#pragma unroll
+    for (int e = 0; e < 4 * G; ++e) acc[e / 4][e % 4] = e == at ? v : acc[e / 4][e % 4];
+  }
+}
+
+// One output of the direct sr = 1 convolution (dir 0: F_t x, 1: F_t^T r), its order of
+// sums: one kernel column, then the total.  taps: the frame's coefficient table.
+__device__ inline float cell_direct(const float* __restrict__ taps, const float* __restrict__ in,
+                                    int H, int W, int k, int l, int dir) {
+  constexpr int c = (CELL_K - 1) / 2;
+  float sum = 0.f;
+#pragma unroll 1
+  for (int b = 0; b < CELL_K; ++b) {
+    const int x = dir == 0 ? l + c - b : l - c + b;
+    float part = 0.f;
+#pragma unroll 1
+    for (int a = 0; a < CELL_K; ++a) {
+      const int y = dir == 0 ? k + c - a : k - c + a;
+      const float v = y >= 0 && y < H && x >= 0 && x < W ? in[(int64_t)y * W + x] : 0.f;
+      part = fmaf(taps[b * TAB_LD + a], v, part);
+    }
+    sum += part;
+  }
+  return sum;
+}
+
 __device__ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // Four consecutive values of row `row` from column `col` (clamped into the

@@ -85,6 +85,12 @@ __device__ inline void cell_fwd_body(const MfmaLaunch& a, const int tile, const 
     const float* ut = a.u ? a.u + (int64_t)t * N : nullptr;
     CellWeights<C> hook{ut, a.H, a.W, p, vec, {}};
     cell_frame<C>(im, it, PLANE, T, acc, hook);
+    if constexpr (F::PREC == EM_FP32)
+      cell_repair(acc, [&](int g, int i) EM_INLINE {
+        const int k = p.row0 + 4 * g, l = p.col + i;
+        return k < a.H && l < a.W ? cell_direct(a.taps + (int64_t)t * CELL_K * TAB_LD, a.in, a.H, a.W, k, l, 0)
+                                  : 0.f;
+      });
     const float* yt = (STUDENT || (ll && ut)) ? a.y + (int64_t)t * N : nullptr;
     float* ot = a.out ? a.out + (int64_t)t * N : nullptr;
 #pragma unroll
@@ -203,6 +209,15 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
   f32x4 sum[C::G];
 #pragma unroll
   for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
+  if constexpr (F::PREC == EM_FP32)
+    cell_repair(sum, [&](int g, int i) EM_INLINE {
+      const int k = p.row0 + 4 * g, l = p.col + i;
+      float s = 0.f;
+      if (k < a.H && l < a.W)
+        for (int t = t0; t < t1; ++t)
+          s += cell_direct(a.taps + (int64_t)t * CELL_K * TAB_LD, a.in + (int64_t)t * N, a.H, a.W, k, l, 1);
+      return s;
+    });
   cell_adj_epilogue<C>(a, sum, p, tile, group, red);
 }
 
@@ -305,7 +320,7 @@ size_t cell_table_bytes(int precision, int n) {
 // The BF16 split form takes its band for jobs whose PSFs passed the band check,
 // and not in serving.
 hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
-  if (a.r16 != nullptr) return hipErrorInvalidValue;
+  if (a.r16 != nullptr || (precision == EM_FP32 && a.taps == nullptr)) return hipErrorInvalidValue;
   const int kind = dir == 1 ? K_ADJ : a.out_y ? K_FWD_T : K_FWD;
   switch (precision) {
     case EM_FP32: return launch_one<EM_FP32, false>(kind, grid, a, s);

@@ -53,6 +53,43 @@ __device__ inline float box_kernel(const float* __restrict__ h, int K, int a, in
   return (float)v;
 }
 
+// One output of the direct convolutions with the 44 x 44 kernel, as cell_direct.
+// H, W: the frame grid; the forward's image is on the latent grid.
+__device__ inline float cell2_direct_fwd(const float* __restrict__ taps, const float* __restrict__ x,
+                                         int H, int W, int I, int J) {
+  float sum = 0.f;
+#pragma unroll 1
+  for (int b = 0; b < CELL2_KC; ++b) {
+    const int l = 2 * J + CELL2_KC / 2 - b;
+    float part = 0.f;
+#pragma unroll 1
+    for (int a = 0; a < CELL2_KC; ++a) {
+      const int k = 2 * I + CELL2_KC / 2 - a;
+      const float v = k >= 0 && k < 2 * H && l >= 0 && l < 2 * W ? x[(int64_t)k * 2 * W + l] : 0.f;
+      part = fmaf(taps[b * TAB_LD + a], v, part);
+    }
+    sum += part;
+  }
+  return sum;
+}
+__device__ inline float cell2_direct_adj(const float* __restrict__ taps, const float* __restrict__ r,
+                                         int H, int W, int k, int l) {
+  float sum = 0.f;
+#pragma unroll 1
+  for (int b = l & 1; b < CELL2_KC; b += 2) {
+    const int J = (l + b - CELL2_KC / 2) / 2;   // even and -22 or more: -11 at least
+    float part = 0.f;
+#pragma unroll 1
+    for (int a = k & 1; a < CELL2_KC; a += 2) {
+      const int I = (k + a - CELL2_KC / 2) / 2;
+      const float v = I >= 0 && I < H && J >= 0 && J < W ? r[(int64_t)I * W + J] : 0.f;
+      part = fmaf(taps[b * TAB_LD + a], v, part);
+    }
+    sum += part;
+  }
+  return sum;
+}
+
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
@@ -126,6 +163,12 @@ __device__ inline void cell2_fwd_body(const MfmaLaunch& a, const int tile, const
     cell_frame<C>(im, it, PLANE, T, acc, hook);
     const int t = t0 + CELL2_FQ * q + (lane >> 4);
     if (t >= t1 || col >= a.W) continue;
+    cell_repair(acc, [&](int g, int e) EM_INLINE {
+      const int I = row + 2 * g + (e >> 1), J = col + (e & 1);
+      return I < a.H && J < a.W
+                 ? cell2_direct_fwd(a.taps + (int64_t)t * CELL2_KC * TAB_LD, a.in, a.H, a.W, I, J)
+                 : 0.f;
+    });
     const float* ut = a.u ? a.u + (int64_t)t * N : nullptr;
     const float* yt = (STUDENT || (ll && ut)) ? a.y + (int64_t)t * N : nullptr;
     float* ot = a.out ? a.out + (int64_t)t * N : nullptr;
@@ -373,6 +416,14 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
 #pragma unroll
   for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
   const CellLane p{k0 + 4 * c + (lane >> 4), l0 + wc * 64 + 4 * (lane & 15)};
+  cell_repair(sum, [&](int g, int i) EM_INLINE {
+    const int k = p.row0 + C::RS * g, l = p.col + i;
+    float s = 0.f;
+    if (k < a.H && l < a.W)
+      for (int t = t0; t < t1; ++t)
+        s += cell2_direct_adj(a.taps + (int64_t)t * CELL2_KC * TAB_LD, a.in + (int64_t)t * Nf, H, W, k, l);
+    return s;
+  });
   cell_adj_epilogue<C>(a, sum, p, tile, group, red);
 }
 
@@ -430,7 +481,7 @@ hipError_t launch_cell2_tables(const Geometry& g, const float* psf, void* tab_fw
 }
 
 bool cell2_desc_ok(const Geometry& g, int dir, int tiles, int groups, const MfmaLaunch& a) {
-  if (a.r16 != nullptr) return false;
+  if (a.r16 != nullptr || a.taps == nullptr) return false;
   return dir == 0 ? a.H == g.Hf && a.W == g.Wf && (groups == 1 || a.fpg % CELL2_FQ == 0) &&
                         launch_grid_ok(tiles, groups, a.ntiles, a.n, a.fpg, a.H, a.W, cell2_fwd_tile_h(),
                                        cell2_fwd_tile_w())

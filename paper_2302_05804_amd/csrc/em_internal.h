@@ -164,6 +164,9 @@ struct MfmaLaunch {
   // BF16 split, K = 43: the PSF's lo part on the central kernel rows only (the
   // job's PSFs passed the band check at set-up)
   int lo_band;
+  // FP32: the coefficient tables of the direct convolution, for the outputs that
+  // infinite or NaN operands reach
+  const float* taps;
 };
 // BF16 split, sr = 1, K = 43: counts in *flag the frames whose PSF keeps more
 // than 1/16 of its mass outside the kernel rows that take the lo part

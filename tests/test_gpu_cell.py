@@ -160,3 +160,30 @@ def test_fp32_frame_sums(sr, hf, wf, n, groups):
     log(f"sr={sr} {n} x {hf} x {wf}: largest error of the frame sum {err:.3f} x 2^-24")
     ctx.close()
     assert err <= groups + 0.01
+
+
+@pytest.mark.parametrize("sr", [1, 2])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_fp32_operators_with_non_finite_pixels(sr, bad):
+    """Pixels that are infinite or NaN reach the outputs of their 43 x 43 support (44 x
+    44 latent pixels for sr = 2) and no others.  All taps are positive, so an infinity
+    gives infinities, as a plain sum does."""
+    em = _em()
+    n, H, W, K = 3, 270 // sr, 390 // sr, 43
+    rng = np.random.default_rng(77)
+    psf = rng.uniform(0.1, 1, (n, K, K)).astype(np.float32)
+    psf /= psf.sum(axis=(1, 2), keepdims=True)
+    x = rng.uniform(1, 2, (sr * H, sr * W)).astype(np.float32)
+    r = rng.uniform(-1, 1, (n, H, W)).astype(np.float32)
+    x[0, 7] = x[131, 258] = bad
+    r[1, 60, 90] = r[2, 0, W - 1] = bad
+    p = em.Problem.make(n, H, W, K, sr=sr)
+    m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy().astype(np.float64)
+    s = em.adjoint_op(p, to_dev(psf), to_dev(r)).cpu().numpy().astype(np.float64)
+    for t in range(n):
+        xa, ra = np.nan_to_num(np.abs(x), posinf=0), np.nan_to_num(np.abs(r[t]), posinf=0)
+        for got, want, absum in ((m[t], oracle.forward(psf[t], x, sr), oracle.forward(psf[t], xa, sr)),
+                                 (s[t], oracle.adjoint(psf[t], r[t], sr), oracle.adjoint(psf[t], ra, sr))):
+            fin = np.isfinite(want)
+            assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fin], want[~fin], equal_nan=True)
+            assert (np.abs(got[fin] - want[fin]) <= (FP32_BOUND + 2.0 ** -24) * absum[fin]).all()
