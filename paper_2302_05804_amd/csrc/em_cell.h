@@ -30,9 +30,12 @@
 // -> 1.18 ms, adjoint 2.17 -> 1.01 ms against one-dimensional Toeplitz operands
 // (alone on the card; 272 tiles in one frame group, two rounds, took 1.77 ms).
 //
-// FP32 parts: a value is hi + mid + lo, each the bf16 nearest to what is left.  All
-// 24 bits are in them from 2^-109 on; below, the last part meets the smallest bf16,
-// 2^-133.  A first part that would round to infinity is clamped.
+// FP32 parts: a value times 2^16 is hi + mid + lo, each the bf16 nearest to what is
+// left.  With that factor the last bit of every binary32 number, 2^-149, is a bf16
+// (the smallest is 2^-133; the matrix cores take subnormal bf16 as they are), so every
+// finite operand is held exactly.  A tile of the image with a value of 2^60 or more
+// takes 2^-32 instead, so that sums do not overflow; what it then cuts off is below
+// 2^-102, and sums below 2^-40 are formed another way (cell_finish).
 //
 // The 48 window columns of a row are one 32-wide chunk ("main") and a 16-wide
 // "tail"; the tails of rows j and j + 1 of a class (image rows 4 s + E and
@@ -87,15 +90,33 @@ struct Prec<EM_FP32> {
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-// Parts of two FP32 values, packed bf16 pairs.  EM_FP32: the first part of a value
-// above the largest bf16 is that one, not infinity.
+// EM_FP32: the factors of the operands.
+constexpr float CELL_UP = 0x1p16f;       // the taps; an image tile of values below 2^60
+constexpr float CELL_UP_BIG = 0x1p-32f;  // any other image tile
+__device__ inline float cell_up(bool big) { return big ? CELL_UP_BIG : CELL_UP; }
+__device__ inline float cell_least(bool big) { return big ? 0x1p-40f : 0.f; }
+// what undoes them in a sum of products
+__device__ inline float cell_down(bool big) { return big ? 0x1p16f : 0x1p-32f; }
+// |v| >= 2^60, infinite or NaN, for the largest of several `bits`
+__device__ inline uint32_t cell_mag(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+__device__ inline bool cell_big(uint32_t bits) { return bits >= (127u + 60u) << 23; }
+// True in every thread where `mine` is in one of the workgroup's NW waves; a barrier.
+// flags: LDS, not written again before the next barrier.
+template <int NW>
+__device__ inline bool cell_any(bool mine, int w, int* flags) {
+  if ((threadIdx.x & 63) == 0) flags[w] = 0;
+  if (__any(mine) && (threadIdx.x & 63) == 0) flags[w] = 1;
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) any |= flags[i];
+  return __builtin_amdgcn_readfirstlane(any) != 0;
+}
+
+// Parts of two values (FP32: with their factor), packed bf16 pairs.
 template <int PREC>
 __device__ inline void cell_split2(f32x2 v, uint32_t (&q)[Prec<PREC>::NB]) {
-  constexpr float M = 3.3895313892515355e38f;
-  f32x2 c = v;
-  if constexpr (PREC == EM_FP32)
-    c = f32x2{__builtin_amdgcn_fmed3f(v.x, -M, M), __builtin_amdgcn_fmed3f(v.y, -M, M)};
-  bf16x2 h = __builtin_convertvector(c, bf16x2);
+  bf16x2 h = __builtin_convertvector(v, bf16x2);
   q[0] = __builtin_bit_cast(uint32_t, h);
 #pragma unroll
   for (int p = 1; p < Prec<PREC>::NB; ++p) {
@@ -229,6 +250,7 @@ struct CellTab {
   const typename F::frag* tab;
   int unit, units, w;
   CellSlots<F> slots;
+  double down;   // FP32 adjoint: what undoes the factors of the current frame's operands
 };
 
 // Work added at the unit boundaries of a frame (0 .. UPF - 1).  wait(b), before
@@ -260,9 +282,9 @@ __device__ inline void cell_boundary(CellTab<typename C::F>& T, int boundary, Ho
 // group, took x after two iterations from 1.14e-7, with groups of three frames in the
 // direct convolution, to 1.44e-7).
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-__device__ EM_INLINE inline void cell_add(f32x4& sum, const f32x4& v) { sum += v; }
-__device__ EM_INLINE inline void cell_add(f64x4& sum, const f32x4& v) {
-  sum += __builtin_convertvector(v, f64x4);
+__device__ EM_INLINE inline void cell_add(f32x4& sum, const f32x4& v, double) { sum += v; }
+__device__ EM_INLINE inline void cell_add(f64x4& sum, const f32x4& v, double down) {
+  sum += __builtin_convertvector(v, f64x4) * down;
 }
 template <bool LEVELS>
 using CellSum = std::conditional_t<LEVELS, f64x4, f32x4>;
@@ -346,7 +368,7 @@ __device__ __attribute__((always_inline)) inline void cell_class(
   });
   if constexpr (F::LEVELS)
     static_for<G>([&](auto gc) EM_INLINE {
-      cell_add(acc[gc], cls[gc] + (big[gc] + small[gc]));
+      cell_add(acc[gc], cls[gc] + (big[gc] + small[gc]), T.down);
       // add now: sunk to the frame's end, the addends of every class would be spilled
       __asm__ volatile("" : "+v"(acc[gc]));
     });
@@ -381,11 +403,11 @@ __device__ inline CellFragId cell_frag_id(int u, int frag) {
   return id;
 }
 
-// Part `part` of one value (0 where there is none).
+// Part `part` of one tap (0 where there is none).
 template <int PREC>
 __device__ inline unsigned short cell_part(float v, int part) {
   uint32_t q[Prec<PREC>::NB];
-  cell_split2<PREC>(f32x2{v, 0.f}, q);
+  cell_split2<PREC>(f32x2{PREC == EM_FP32 ? v * CELL_UP : v, 0.f}, q);
   uint32_t out = 0;
 #pragma unroll
   for (int x = 0; x < Prec<PREC>::NB; ++x) out = x == part ? q[x] : out;
@@ -416,18 +438,23 @@ __device__ inline int cell_tail_off() {
          (gq >> 1) * 4 * C::PITCH + 32 + 8 * (gq & 1);
 }
 
-// FP32: an infinity or NaN in an operand does not survive the split into parts (inf -
-// inf) and meets the zeros of the table around the 43 x 43 taps, so it makes NaN of
-// every output whose 46 x 48 window holds it.  The outputs that are not finite are
-// formed once more as the direct convolution does, one at a time: `value(g, i)` for
-// element i of cell row g.  (The BF16 forms leave them: NaN up to three pixels outside
-// the support.  With this step their adjoint spilled: 33 x 1999 x 2111 1.04 -> 1.09 ms.)
+// FP32: undoes the operands' factors.  An infinity or NaN in an operand does not survive
+// the split into parts (inf - inf) and meets the zeros of the table around the 43 x 43
+// taps, so it makes NaN of every output whose 46 x 48 window holds it.  The outputs
+// that are not finite are formed once more as the direct convolution does, one at a
+// time: `value(g, i)` for element i of cell row g; so are those below `least` (in a
+// tile of the lower factor, whose smallest operands are cut off).  The BF16 forms leave
+// them: NaN up to three pixels outside the support (with this step their adjoint
+// spilled: 33 x 1999 x 2111 1.04 -> 1.09 ms).
 template <int G, class Fn>
-__device__ EM_INLINE inline void cell_repair(f32x4 (&acc)[G], Fn&& value) {
+__device__ EM_INLINE inline void cell_finish(f32x4 (&acc)[G], float down, float least, Fn&& value) {
   uint32_t bad = 0;
 #pragma unroll
-  for (int e = 0; e < 4 * G; ++e)
-    bad |= __builtin_isfinite(acc[e / 4][e % 4]) ? 0u : 1u << e;
+  for (int e = 0; e < 4 * G; ++e) {
+    acc[e / 4][e % 4] *= down;
+    const float m = fabsf(acc[e / 4][e % 4]);
+    bad |= m >= least && m <= 3.4028235e38f ? 0u : 1u << e;
+  }
   while (bad != 0) {
     const int at = __ffs(bad) - 1;
     bad &= bad - 1;
@@ -447,7 +474,7 @@ __device__ inline float cell_direct(const float* __restrict__ taps, const float*
   for (int b = 0; b < CELL_K; ++b) {
     const int x = dir == 0 ? l + c - b : l - c + b;
     float part = 0.f;
-#pragma unroll 1
+#pragma unroll 4
     for (int a = 0; a < CELL_K; ++a) {
       const int y = dir == 0 ? k + c - a : k - c + a;
       const float v = y >= 0 && y < H && x >= 0 && x < W ? in[(int64_t)y * W + x] : 0.f;
@@ -528,7 +555,17 @@ struct CellTile {
       }
     }
   }
-  __device__ void store(unsigned short* sh) {
+  // FP32: whether the tile takes the lower factor (a lane's share of the answer)
+  __device__ bool big() const {
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) m = max(m, cell_mag(v[i][x]));
+    return cell_big(m);
+  }
+  // up: the factor of the values (FP32)
+  __device__ void store(unsigned short* sh, float up) {
     int g = gx;
     __asm__ volatile("" : "+v"(g));
     if (!inner) {
@@ -553,8 +590,10 @@ struct CellTile {
       if ((i + 1) * C::NW > C::ROWS && row >= C::ROWS) break;
       const bool iny = gy >= 0 && gy < H;
       uint32_t a[F::NB], b[F::NB];
-      cell_split2<F::PREC>(iny ? f32x2{v[i][0], v[i][1]} : f32x2{0.f, 0.f}, a);
-      cell_split2<F::PREC>(iny ? f32x2{v[i][2], v[i][3]} : f32x2{0.f, 0.f}, b);
+      f32x4 o = v[i];
+      if constexpr (F::PREC == EM_FP32) o = f32x4{o[0] * up, o[1] * up, o[2] * up, o[3] * up};
+      cell_split2<F::PREC>(iny ? f32x2{o[0], o[1]} : f32x2{0.f, 0.f}, a);
+      cell_split2<F::PREC>(iny ? f32x2{o[2], o[3]} : f32x2{0.f, 0.f}, b);
 #pragma unroll
       for (int p = 0; p < F::NA; ++p)
         *reinterpret_cast<uint2*>(dst + p * PLANE + C::NW * i * C::PITCH) = make_uint2(a[p], b[p]);

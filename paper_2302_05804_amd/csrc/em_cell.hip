@@ -46,19 +46,22 @@ __device__ inline void cell_fwd_body(const MfmaLaunch& a, const int tile, const 
   __shared__ __align__(16) frag slot0[F::NFU * 64];
   __shared__ __align__(16) frag slot1[F::NFU * 64];
   __shared__ double red[C::NW];
+  __shared__ int flags[C::NW];
   const int tiles_x = (a.W + C::TW - 1) / C::TW;
   const int k0 = (tile / tiles_x) * C::TH, l0 = (tile % tiles_x) * C::TW;
   const int t0 = group * a.fpg;
   const int t1 = min(a.n, t0 + a.fpg);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   CellTab<F> T{reinterpret_cast<const frag*>(a.tab) + (int64_t)t0 * F::FRAME, 0,
-               (t1 - t0) * F::UPF, w, {slot0, slot1}};
+               (t1 - t0) * F::UPF, w, {slot0, slot1}, 1.0};
   cell_issue_unit<C>(T.tab, 0, w, slot0);
   cell_issue_unit<C>(T.tab, 1, w, slot1);
+  bool big = false;
   {
     CellTile<C> tl(a.H, a.W, k0, l0, w);
     tl.load(a.in);
-    tl.store(sh);
+    if constexpr (F::PREC == EM_FP32) big = cell_any<C::NW>(tl.big(), w, flags);
+    tl.store(sh, cell_up(big));
   }
   cell_wait<0>();
   __syncthreads();
@@ -86,7 +89,7 @@ __device__ inline void cell_fwd_body(const MfmaLaunch& a, const int tile, const 
     CellWeights<C> hook{ut, a.H, a.W, p, vec, {}};
     cell_frame<C>(im, it, PLANE, T, acc, hook);
     if constexpr (F::PREC == EM_FP32)
-      cell_repair(acc, [&](int g, int i) EM_INLINE {
+      cell_finish(acc, cell_down(big), cell_least(big), [&](int g, int i) EM_INLINE {
         const int k = p.row0 + 4 * g, l = p.col + i;
         return k < a.H && l < a.W ? cell_direct(a.taps + (int64_t)t * CELL_K * TAB_LD, a.in, a.H, a.W, k, l, 0)
                                   : 0.f;
@@ -168,6 +171,7 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
   __shared__ __align__(16) frag slot0[F::NFU * 64];
   __shared__ __align__(16) frag slot1[F::NFU * 64];
   __shared__ double red[2 * C::NW];
+  __shared__ int flags[C::NW];
   const int tiles_x = (a.W + C::TW - 1) / C::TW;
   const int k0 = (tile / tiles_x) * C::TH, l0 = (tile % tiles_x) * C::TW;
   const int64_t N = (int64_t)a.H * a.W;
@@ -175,7 +179,7 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
   const int t1 = min(a.n, t0 + a.fpg);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   CellTab<F> T{reinterpret_cast<const frag*>(a.tab) + (int64_t)t0 * F::FRAME, 0,
-               (t1 - t0) * F::UPF, w, {slot0, slot1}};
+               (t1 - t0) * F::UPF, w, {slot0, slot1}, 1.0};
   cell_issue_unit<C>(T.tab, 0, w, slot0);
   cell_issue_unit<C>(T.tab, 1, w, slot1);
   const CellLane p = cell_lane<C>(k0, l0);
@@ -187,8 +191,16 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
   for (int g = 0; g < C::G; ++g) acc[g] = Sum{0, 0, 0, 0};
   Hook hook{CellTile<C>(a.H, a.W, k0, l0, w), a.in + (int64_t)t0 * N};
   hook.tl.load(hook.next);
+  bool any_big = false;
   for (int t = t0; t < t1; ++t) {
-    hook.tl.store(sh);
+    float up = 1.f;
+    if constexpr (F::PREC == EM_FP32) {
+      const bool big = cell_any<C::NW>(hook.tl.big(), w, flags);   // every wave is done with the tile
+      up = cell_up(big);
+      T.down = cell_down(big);
+      any_big |= big;
+    }
+    hook.tl.store(sh, up);
     cell_wait<0>();
     __syncthreads();
     hook.next = a.in + (int64_t)min(t + 1, t1 - 1) * N;
@@ -203,14 +215,14 @@ __device__ inline void cell_adj_body(const MfmaLaunch& a, const int tile, const 
 #pragma unroll
       for (int g = 0; g < C::G; ++g) acc[g] += accf[g];
     }
-    __syncthreads();   // every wave is done with the tile
+    if constexpr (F::PREC != EM_FP32) __syncthreads();   // every wave is done with the tile
   }
   cell_wait<0>();   // the copies issued past the last unit
   f32x4 sum[C::G];
 #pragma unroll
   for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
   if constexpr (F::PREC == EM_FP32)
-    cell_repair(sum, [&](int g, int i) EM_INLINE {
+    cell_finish(sum, 1.f, cell_least(any_big), [&](int g, int i) EM_INLINE {
       const int k = p.row0 + 4 * g, l = p.col + i;
       float s = 0.f;
       if (k < a.H && l < a.W)

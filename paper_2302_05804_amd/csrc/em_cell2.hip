@@ -62,7 +62,7 @@ __device__ inline float cell2_direct_fwd(const float* __restrict__ taps, const f
   for (int b = 0; b < CELL2_KC; ++b) {
     const int l = 2 * J + CELL2_KC / 2 - b;
     float part = 0.f;
-#pragma unroll 1
+#pragma unroll 4
     for (int a = 0; a < CELL2_KC; ++a) {
       const int k = 2 * I + CELL2_KC / 2 - a;
       const float v = k >= 0 && k < 2 * H && l >= 0 && l < 2 * W ? x[(int64_t)k * 2 * W + l] : 0.f;
@@ -79,7 +79,7 @@ __device__ inline float cell2_direct_adj(const float* __restrict__ taps, const f
   for (int b = l & 1; b < CELL2_KC; b += 2) {
     const int J = (l + b - CELL2_KC / 2) / 2;   // even and -22 or more: -11 at least
     float part = 0.f;
-#pragma unroll 1
+#pragma unroll 2
     for (int a = k & 1; a < CELL2_KC; a += 2) {
       const int I = (k + a - CELL2_KC / 2) / 2;
       const float v = I >= 0 && I < H && J >= 0 && J < W ? r[(int64_t)I * W + J] : 0.f;
@@ -127,6 +127,7 @@ __device__ inline void cell2_fwd_body(const MfmaLaunch& a, const int tile, const
   __shared__ __align__(16) frag slot0[F::NFU * 64];
   __shared__ __align__(16) frag slot1[F::NFU * 64];
   __shared__ double red[C::NW];
+  __shared__ int flags[C::NW];
   const int tiles_x = (a.W + TW - 1) / TW;
   const int I0 = (tile / tiles_x) * TH, J0 = (tile % tiles_x) * TW;
   const int t0 = group * a.fpg;
@@ -134,13 +135,15 @@ __device__ inline void cell2_fwd_body(const MfmaLaunch& a, const int tile, const
   const int quads = (t1 - t0 + CELL2_FQ - 1) / CELL2_FQ;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   CellTab<F> T{reinterpret_cast<const frag*>(a.tab) + (int64_t)(t0 / CELL2_FQ) * F::FRAME, 0,
-               quads * F::UPF, w, {slot0, slot1}};
+               quads * F::UPF, w, {slot0, slot1}, 1.0};
   cell_issue_unit<C>(T.tab, 0, w, slot0);
   cell_issue_unit<C>(T.tab, 1, w, slot1);
+  bool big;
   {
     CellTile<C> tl(2 * a.H, 2 * a.W, 2 * I0, 2 * J0, w);
     tl.load(a.in);
-    tl.store(sh);
+    big = cell_any<C::NW>(tl.big(), w, flags);
+    tl.store(sh, cell_up(big));
   }
   cell_wait<0>();
   __syncthreads();
@@ -163,7 +166,7 @@ __device__ inline void cell2_fwd_body(const MfmaLaunch& a, const int tile, const
     cell_frame<C>(im, it, PLANE, T, acc, hook);
     const int t = t0 + CELL2_FQ * q + (lane >> 4);
     if (t >= t1 || col >= a.W) continue;
-    cell_repair(acc, [&](int g, int e) EM_INLINE {
+    cell_finish(acc, cell_down(big), cell_least(big), [&](int g, int e) EM_INLINE {
       const int I = row + 2 * g + (e >> 1), J = col + (e & 1);
       return I < a.H && J < a.W
                  ? cell2_direct_fwd(a.taps + (int64_t)t * CELL2_KC * TAB_LD, a.in, a.H, a.W, I, J)
@@ -294,8 +297,16 @@ __device__ inline Fr cell2_ld8(const unsigned short* p) {
 template <class C>
 struct Adj2Tile {
   float v[C::NPT];
+  // as CellTile::big
+  __device__ bool big() const {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < C::NPT; ++k) m = max(m, cell_mag(v[k]));
+    return cell_big(m);
+  }
   template <bool STORE>
-  __device__ void pass(const float* __restrict__ src, int H, int W, int i0, int j0, unsigned short* sh) {
+  __device__ void pass(const float* __restrict__ src, int H, int W, int i0, int j0, unsigned short* sh,
+                       float up) {
     int e = threadIdx.x;
     __asm__ volatile("" : "+v"(e));   // the address arithmetic stays here
 #pragma unroll
@@ -307,7 +318,7 @@ struct Adj2Tile {
       } else if (e < C::PLANE) {
         const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
         uint32_t q[C::NB];
-        cell_split2<C::PREC>(f32x2{in ? v[k] : 0.f, 0.f}, q);
+        cell_split2<C::PREC>(f32x2{in ? v[k] * up : 0.f, 0.f}, q);
 #pragma unroll
         for (int p = 0; p < C::NA; ++p) sh[p * C::PLANE + e] = (unsigned short)q[p];
       }
@@ -318,7 +329,7 @@ struct Adj2Tile {
 // One class: `im[P]` this lane's piece of product P at step 0 (window row E).
 template <class C>
 __device__ EM_INLINE inline void cell2_class(const unsigned short* const (&im)[3],
-                                             const typename C::frag* slot, f64x4 (&acc)[C::G]) {
+                                             const typename C::frag* slot, f64x4 (&acc)[C::G], double down) {
   using frag = typename C::frag;
   constexpr int G = C::G;
   const int lane = threadIdx.x & 63;
@@ -348,7 +359,7 @@ __device__ EM_INLINE inline void cell2_class(const unsigned short* const (&im)[3
     });
   });
   static_for<G>([&](auto gc) EM_INLINE {
-    cell_add(acc[gc], big[gc] + small[gc]);
+    cell_add(acc[gc], big[gc] + small[gc], down);
     __asm__ volatile("" : "+v"(acc[gc]));   // add now, as in cell_class
   });
 }
@@ -364,6 +375,7 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
   __shared__ __align__(16) frag slot0[C::NF * 64];
   __shared__ __align__(16) frag slot1[C::NF * 64];
   __shared__ double red[2 * C::NW];
+  __shared__ int flags[C::NW];
   const int tiles_x = (a.W + C::TW - 1) / C::TW;            // a.H, a.W: latent grid
   const int k0 = (tile / tiles_x) * C::TH, l0 = (tile % tiles_x) * C::TW;
   const int H = a.H / 2, W = a.W / 2;
@@ -377,8 +389,9 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
   cell2_issue<C>(tab, w, slot0);
   Adj2Tile<C> tl;
   const int i0 = k0 / 2 - 11, j0 = l0 / 2 - 11;
-  tl.template pass<false>(a.in + (int64_t)t0 * Nf, H, W, i0, j0, nullptr);
-  tl.template pass<true>(nullptr, H, W, i0, j0, sh[0]);
+  tl.template pass<false>(a.in + (int64_t)t0 * Nf, H, W, i0, j0, nullptr, 0.f);
+  bool big = cell_any<C::NW>(tl.big(), w, flags), any_big = false;
+  tl.template pass<true>(nullptr, H, W, i0, j0, sh[0], cell_up(big));
   cell_wait<0>();
   __syncthreads();
   // this lane's piece x = lane / 16 of product P: piece 4 P + x of rows s .. s + 3
@@ -395,19 +408,22 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
     const unsigned short* base = sh[(t - t0) & 1];
     const int unit = 2 * (t - t0);
     cell2_issue<C>(tab + (int64_t)(unit + 1) * C::NF * 64, w, slot1);
-    tl.template pass<false>(a.in + (int64_t)min(t + 1, t1 - 1) * Nf, H, W, i0, j0, nullptr);
+    tl.template pass<false>(a.in + (int64_t)min(t + 1, t1 - 1) * Nf, H, W, i0, j0, nullptr, 0.f);
+    const double down = cell_down(big);
+    any_big |= big;
     {
       const unsigned short* const im[3] = {base + off[0], base + off[1], base + off[2]};
-      cell2_class<C>(im, slot0, acc);
+      cell2_class<C>(im, slot0, acc, down);
     }
     cell_wait<0>();
-    __syncthreads();   // slot 1 has landed, slot 0 and the other tile are free
+    big = cell_any<C::NW>(tl.big(), w, flags);   // slot 1 has landed, slot 0 and the other tile are free
     cell2_issue<C>(tab + (int64_t)min(unit + 2, units - 2) * C::NF * 64, w, slot0);
-    tl.template pass<true>(nullptr, H, W, i0, j0, sh[(t - t0 + 1) & 1]);
+    tl.template pass<true>(nullptr, H, W, i0, j0, sh[(t - t0 + 1) & 1],
+                           cell_up(big));
     {
       const unsigned short* const im[3] = {base + C::PITCH + off[0], base + C::PITCH + off[1],
                                            base + C::PITCH + off[2]};
-      cell2_class<C>(im, slot1, acc);
+      cell2_class<C>(im, slot1, acc, down);
     }
     cell_wait<0>();
     __syncthreads();   // the next tile and slot 0 are complete
@@ -416,7 +432,7 @@ __device__ inline void cell2_adj_body(const MfmaLaunch& a, const int tile, const
 #pragma unroll
   for (int g = 0; g < C::G; ++g) sum[g] = __builtin_convertvector(acc[g], f32x4);
   const CellLane p{k0 + 4 * c + (lane >> 4), l0 + wc * 64 + 4 * (lane & 15)};
-  cell_repair(sum, [&](int g, int i) EM_INLINE {
+  cell_finish(sum, 1.f, cell_least(any_big), [&](int g, int i) EM_INLINE {
     const int k = p.row0 + C::RS * g, l = p.col + i;
     float s = 0.f;
     if (k < a.H && l < a.W)

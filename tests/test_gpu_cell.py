@@ -187,3 +187,31 @@ def test_fp32_operators_with_non_finite_pixels(sr, bad):
             fin = np.isfinite(want)
             assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fin], want[~fin], equal_nan=True)
             assert (np.abs(got[fin] - want[fin]) <= (FP32_BOUND + 2.0 ** -24) * absum[fin]).all()
+
+
+@pytest.mark.parametrize("sr", [1, 2])
+@pytest.mark.parametrize("xs,fs", [(1e-37, 1.0), (1e-41, 1.0), (1e4, 1e-37), (1e25, 1e-38), (1e-20, 1e-14),
+                                   (2e18, 1.0), (1e36, 1e-1)])
+def test_fp32_tiny_and_huge_operands(sr, xs, fs):
+    """Operands down to the subnormal numbers are held exactly: the error is that of
+    the sum (FP32_BOUND of the absolute sum; one tap more for the box) and of rounding
+    the result, half of 2^-149 at least."""
+    em = _em()
+    n, H, W, K = 2, 132 // sr, 260 // sr, 43
+    rng = np.random.default_rng(31)
+    psf = rng.uniform(0, 1, (n, K, K))
+    psf = (psf / psf.sum(axis=(1, 2), keepdims=True) * 40 * fs).astype(np.float32)
+    x = (rng.uniform(0.5, 1, (sr * H, sr * W)) * xs).astype(np.float32)
+    r = (rng.uniform(0.5, 1, (n, H, W)) * xs).astype(np.float32)
+    if fs < 1e-30:
+        psf[1] = 0
+        psf[1, 5, 30] = 3.3 * fs
+    p = em.Problem.make(n, H, W, K, sr=sr)
+    m = em.forward_op(p, to_dev(psf), to_dev(x)).cpu().numpy().astype(np.float64)
+    s = em.adjoint_op(p, to_dev(psf), to_dev(r)).cpu().numpy().astype(np.float64)
+    for t in range(n):
+        for got, want in ((m[t], oracle.forward(psf[t], x, sr)), (s[t], oracle.adjoint(psf[t], r[t], sr))):
+            err = np.abs(got - want)
+            # a box tap is rounded to binary32, where the smallest step is 2^-149
+            tap = 0.5 * 2.0 ** -149 * x.sum(dtype=np.float64) if sr == 2 else 0.0
+            assert (err <= (FP32_BOUND + 2.0 ** -24) * want + 2.0 ** -150 * 1.001 + tap).all()
