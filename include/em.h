@@ -225,16 +225,20 @@ int em_profile(em_ctx* ctx, int32_t n_iter, double* phase_ms);
  * Kernel variants of the matrix-core precisions (tile / wave layouts that
  * compute the same sums; results may differ from one variant to another at the
  * rounding level).  em_variant_count() gives their number; em_set_variants
- * selects one per direction (0 = forward, 1 = adjoint) for ctx.
+ * selects one per direction (0 = forward, 1 = adjoint) for ctx.  Some jobs have
+ * one kernel for all variants of a direction, where the choice has no effect:
+ * BF16 and BF16 split with sr = 1 and K > 15, and FP16 split with sr = 1 where
+ * the image is small.  EM_ENOTSUP for FP32.
  */
 int em_variant_count(void);
 int em_set_variants(em_ctx* ctx, int32_t fwd_variant, int32_t adj_variant);
 
 /*
  * Autotuner: times every variant of the forward and the adjoint kernel on the
- * job's own data (n_rep launches each after one warm-up, HIP events on the
- * job's stream; the iterate x is not modified) and selects the fastest for
- * ctx alone.  Every job starts on variants 0 / 0, whatever other jobs of the
+ * job's own data (n_rep launches each, the variants in turn, after one turn of
+ * warm-up; HIP events on the job's stream; the iterate x is not modified) and
+ * selects the fastest for ctx alone; variant 0, with one time for all, where a
+ * direction has one kernel.  Every job starts on variants 0 / 0, whatever other jobs of the
  * process chose, so its arithmetic never depends on them.  Writes the chosen
  * variants and, if ms != NULL, the mean launch times
  * ms[dir * em_variant_count() + v].  Synchronous.

@@ -1022,60 +1022,62 @@ int em_autotune(em_ctx* c, int32_t n_rep, int32_t* fwd_variant, int32_t* adj_var
   if (c->g.precision == EM_FP32) return fail(EM_ENOTSUP, "variants exist for matrix-core precisions only");
   if (n_rep < 1) return fail(EM_EINVAL, "n_rep must be >= 1");
   const int nv = mfma_variants();
-  hipEvent_t e0, e1;
-  EM_HIP(hipEventCreate(&e0));
-  EM_HIP(hipEventCreate(&e1));
+  std::vector<hipEvent_t> ev(nv + 1, nullptr);
   std::vector<double> t(2 * nv, 0.0);
   int rc = EM_OK;
-  for (int dir = 0; dir < 2 && rc == EM_OK; ++dir) {
-    for (int i = 0; i < nv && rc == EM_OK; ++i) {
-      // The first variant timed runs 4-7% slower than after the others (33 x 4096^2
-      // forward of 4x2 blocks 3.23 first, 3.00 ms later).  FP16 split, sr = 1: that is
-      // variant 2, the slowest, and not variant 0.
-      const int v = c->g.sr == 1 && c->g.precision == EM_FP16_SPLIT ? nv - 1 - i : i;
-      // descriptors of the iteration itself (grid sizes of the right grids)
-      MfmaLaunch m;
-      int tiles, groups;
-      if (dir == 0) {
-        // the forward writes r (and u w y under Student-t noise), which every
-        // iteration recomputes before use
-        fill_forward_mfma(c, &m, true, false);
-        if (c->g.weight_mode == EM_W_STUDENT_T) {
-          m.out_y = c->ry;
-          m.nu = c->g.nu;
-          m.lcst = student_t_lcst((double)c->g.nu);
-        }
-        if (uses_r16(c->g)) {
-          apply_r16(c, &m, 0);
-          if ((rc = r16_scale(c))) break;
-        }
-        tiles = c->pl.fwd_tiles;
-        groups = c->pl.fwd_groups;
-      } else {
-        // the adjoint writes partial planes (never the iterate)
-        fill_adjoint_mfma(c, &m, nullptr);
-        if (uses_r16(c->g)) apply_r16(c, &m, 1);
-        m.fused = 0;
-        m.plane = c->pl.adj_groups > 1 ? c->planes : c->tune;
-        tiles = c->pl.adj_tiles;
-        groups = c->pl.adj_groups;
+  hipError_t e = hipSuccess;
+  for (int i = 0; i <= nv && e == hipSuccess; ++i) e = hipEventCreate(&ev[i]);
+  for (int dir = 0; dir < 2 && rc == EM_OK && e == hipSuccess; ++dir) {
+    // descriptors of the iteration itself (grid sizes of the right grids)
+    MfmaLaunch m;
+    int tiles, groups;
+    if (dir == 0) {
+      // the forward writes r (and u w y under Student-t noise), which every
+      // iteration recomputes before use
+      fill_forward_mfma(c, &m, true, false);
+      if (c->g.weight_mode == EM_W_STUDENT_T) {
+        m.out_y = c->ry;
+        m.nu = c->g.nu;
+        m.lcst = student_t_lcst((double)c->g.nu);
       }
-      for (int k = 0; k <= n_rep && rc == EM_OK; ++k) {
-        if (k == 1) EM_HIP(hipEventRecord(e0, c->stream));
-        hipError_t e = launch_mfma(c->g, dir, v, tiles, groups, m, c->stream);
-        if (e != hipSuccess) rc = fail(EM_EDEVICE, "autotune launch: %s", hipGetErrorString(e));
+      if (uses_r16(c->g)) {
+        apply_r16(c, &m, 0);
+        if ((rc = r16_scale(c))) break;
       }
-      if (rc) break;
-      EM_HIP(hipEventRecord(e1, c->stream));
-      EM_HIP(hipEventSynchronize(e1));
-      float el = 0.f;
-      EM_HIP(hipEventElapsedTime(&el, e0, e1));
-      t[dir * nv + v] = el / n_rep;
+      tiles = c->pl.fwd_tiles;
+      groups = c->pl.fwd_groups;
+    } else {
+      // the adjoint writes partial planes (never the iterate)
+      fill_adjoint_mfma(c, &m, nullptr);
+      if (uses_r16(c->g)) apply_r16(c, &m, 1);
+      m.fused = 0;
+      m.plane = c->pl.adj_groups > 1 ? c->planes : c->tune;
+      tiles = c->pl.adj_tiles;
+      groups = c->pl.adj_groups;
     }
+    // The variants take turns, so that each of them has the clocks of the whole
+    // measurement (timed one after the other, the first one ran 4-7% slower than
+    // after the others), and the first turn is not counted.
+    const int nd = mfma_has_variants(c->g, dir) ? nv : 1;
+    for (int k = 0; k <= n_rep && e == hipSuccess; ++k) {
+      e = hipEventRecord(ev[0], c->stream);
+      for (int v = 0; v < nd && e == hipSuccess; ++v) {
+        e = launch_mfma(c->g, dir, v, tiles, groups, m, c->stream);
+        if (e == hipSuccess) e = hipEventRecord(ev[v + 1], c->stream);
+      }
+      if (e == hipSuccess) e = hipEventSynchronize(ev[nd]);
+      for (int v = 0; v < nd && k > 0 && e == hipSuccess; ++v) {
+        float el = 0.f;
+        e = hipEventElapsedTime(&el, ev[v], ev[v + 1]);
+        t[dir * nv + v] += el / n_rep;
+      }
+    }
+    for (int v = nd; v < nv; ++v) t[dir * nv + v] = t[dir * nv];
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  for (hipEvent_t x : ev)
+    if (x) (void)hipEventDestroy(x);
   if (rc) return rc;
+  if (e != hipSuccess) return fail(EM_EDEVICE, "autotune: %s", hipGetErrorString(e));
   int bf = 0, ba = 0;
   for (int v = 1; v < nv; ++v) {
     if (t[v] < t[bf]) bf = v;

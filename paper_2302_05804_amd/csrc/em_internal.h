@@ -273,6 +273,8 @@ hipError_t launch_forward_batched(int sr, int KT, const FwdLaunch* descs, const 
 hipError_t launch_adjoint_batched(int sr, int KT, const AdjLaunch* descs, const int4* items,
                                   int n_items, int grid, hipStream_t s);
 int mfma_variants();
+// whether the variants of a direction (0 forward, 1 adjoint) are different kernels
+bool mfma_has_variants(const Geometry& g, int dir);
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band = false);
 int mfma_tile_h(const Geometry& g, int dir);   // outputs of a workgroup, sr = 1

@@ -894,6 +894,10 @@ size_t mfma_table_bytes(const Geometry& g, int dir) {
          (size_t)g.n * sizeof(int);
 }
 int mfma_variants() { return 3; }
+// the cell kernels and the 64 x 64 tiles have one layout
+bool mfma_has_variants(const Geometry& g, int dir) {
+  return !uses_cell(g) && !uses_cell2(g) && !(g.sr == 1 && small_tile(g, dir));
+}
 
 namespace {
 // Variants 0, 1, 2 of each direction.  Every job starts on variant 0, so that is
