@@ -3,7 +3,6 @@
 // sr = 1 and kernels padded to 43 x 43, in the BF16 forms and in FP32.
 #include "em_cell.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace em {
@@ -321,13 +320,12 @@ int cell_tile_h(int precision) {
 }
 static_assert(CellOf<EM_FP32, false>::TW == CELL_TILE_W && CellOf<EM_BF16, false>::TW == CELL_TILE_W, "tile");
 
-size_t cell_table_bytes(int precision, int n) {
-  const int64_t lanes = precision == EM_FP32         ? CellForm<EM_FP32, false>::FRAME
-                        : precision == EM_BF16_SPLIT ? std::max(CellForm<EM_BF16_SPLIT, false>::FRAME,
-                                                                CellForm<EM_BF16_SPLIT, true>::FRAME)
-                                                     : CellForm<EM_BF16, false>::FRAME;
-  return (size_t)n * lanes * 16;
-}
+size_t cell_table_bytes(int n) { return (size_t)n * CellForm<EM_FP32, false>::FRAME * 16; }
+template <class F>
+constexpr bool cell_table_fits = F::FRAME * 16 <= (int64_t)mfma_table_frame(KT_LARGE);
+static_assert(cell_table_fits<CellForm<EM_BF16_SPLIT, false>> && cell_table_fits<CellForm<EM_BF16_SPLIT, true>> &&
+                  cell_table_fits<CellForm<EM_BF16, false>>,
+              "the BF16 forms' tables within mfma_table_bytes");
 
 // The BF16 split form takes its band for jobs whose PSFs passed the band check,
 // and not in serving.

@@ -29,7 +29,6 @@
 // tiles on 256 compute units, three of twelve frame slots empty in the forward).
 #include "em_cell.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace em {

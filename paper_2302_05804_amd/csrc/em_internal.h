@@ -219,11 +219,14 @@ struct R16Job {
 hipError_t launch_r16_scale_batched(const R16Job* jobs, int n_jobs, hipStream_t s);
 hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int groups,
                        const MfmaLaunch& a, hipStream_t s);
-int mfma_table_rows(int KT);
+constexpr int mfma_table_rows(int KT) { return 16 * ((KT + 15) / 16); }
+// Toeplitz fragments of one frame and direction: the room of every sr = 1 table of the
+// split forms, also of the cell kernels' (em_cell.hip checks that theirs fit)
+constexpr size_t mfma_table_frame(int KT) { return (size_t)mfma_table_rows(KT) * 4 * 64 * 8 * sizeof(uint16_t); }
 // the 4 x 4 cell kernels (em_cell.hip); cell_tile_h x 128 outputs per workgroup
 int cell_tile_h(int precision);
 constexpr int CELL_TILE_W = 128;
-size_t cell_table_bytes(int precision, int n);
+size_t cell_table_bytes(int n);   // FP32
 hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s);
 hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, const int4* items,
                                int n_items, int grid, hipStream_t s, bool robust);

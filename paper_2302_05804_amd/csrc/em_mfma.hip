@@ -856,8 +856,6 @@ __global__ __launch_bounds__(256) void mfma_table_kernel(const float* psf, int n
   }
 }
 
-int mfma_table_rows(int KT) { return 16 * ((KT + 15) / 16); }
-
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band) {
   if (uses_cell2(g)) return launch_cell2_tables(g, psf, tab_fwd, tab_adj, s);
@@ -888,10 +886,9 @@ int mfma_tile_w(const Geometry& g, int dir) { return small_tile(g, dir) ? MF_SMA
 size_t mfma_table_bytes(const Geometry& g, int dir) {
   if (uses_cell2(g)) return cell2_table_bytes(g.n, dir);
   if (g.sr == 2) return dir == 0 && uses_m2n(g) ? mfma2n_table_bytes(g.n) : mfma2_table_bytes(g.n, dir);
-  if (g.mc32) return cell_table_bytes(g.precision, g.n);
+  if (g.mc32) return cell_table_bytes(g.n);
   // fragments, then one scale exponent per frame
-  return (size_t)g.n * mfma_table_rows(g.KT) * 4 * 64 * 8 * sizeof(uint16_t) +
-         (size_t)g.n * sizeof(int);
+  return (size_t)g.n * (mfma_table_frame(g.KT) + sizeof(int));
 }
 int mfma_variants() { return 3; }
 // the cell kernels and the 64 x 64 tiles have one layout
