@@ -923,10 +923,15 @@ int em_profile(em_ctx* c, int32_t n_iter, double* phase_ms) {
 }
 
 int em_check_plan(const em_problem* p) {
-  Geometry g;
+  Geometry full;
   const char* why = nullptr;
-  if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
-  for (int serving = 0; serving < 2; ++serving) {
+  if (!make_geometry(p, &full, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
+  static const char* const plans[3] = {"plan", "smallest plan", "serving plan"};
+  for (int kind = 0; kind < 3; ++kind) {
+    const char* what = plans[kind];
+    const bool serving = kind == 2;
+    Geometry g = full;
+    if (kind == 1) make_lean(&g);
     if (serving) g.mc32 = g.small16 = g.small32 = 0;
     const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
     em_ctx c{};
@@ -935,7 +940,6 @@ int em_check_plan(const em_problem* p) {
     c.lay = make_layout(g, pl);
     c.ws = reinterpret_cast<char*>(static_cast<uintptr_t>(1) << 20);   // never dereferenced
     em_bind_views(&c);
-    const char* what = serving ? "serving plan" : "plan";
     for (int v = 0; v < (uses_mfma(g) ? mfma_variants() : 1); ++v) {
       c.pl.fwd_variant = c.pl.adj_variant = v;
       if (uses_mfma(g)) {
