@@ -1141,7 +1141,7 @@ int em_forward_op(const em_problem* p, const float* psf, const float* x, float* 
   EM_HIP(launch_reset_counters(flags, s));
   EM_HIP(launch_psf_tables(g, psf, tab, flags, s));
   if (uses_mfma(g)) {
-    EM_HIP(launch_mfma_tables(g, psf, w + L.mtab_fwd, w + L.mtab_adj, s));
+    EM_HIP(launch_mfma_tables(g, psf, w + L.mtab_fwd, nullptr, s));
     MfmaLaunch mm{};
     mm.in = x;
     mm.tab = w + L.mtab_fwd;
@@ -1192,7 +1192,7 @@ int em_adjoint_op(const em_problem* p, const float* psf, const float* r, float* 
   per.adj_fpg = 1;
   per.adj_groups = g.n;
   if (uses_mfma(g)) {
-    EM_HIP(launch_mfma_tables(g, psf, w + L.mtab_fwd, w + L.mtab_adj, s));
+    EM_HIP(launch_mfma_tables(g, psf, nullptr, w + L.mtab_adj, s));
     MfmaLaunch mm{};
     mm.in = r;
     mm.tab = w + L.mtab_adj;

@@ -258,8 +258,8 @@ __global__ __launch_bounds__(C::NT) void cell_batched(const MfmaLaunch* __restri
   }
 }
 
-// Tables of one frame (blockIdx.x), one unit per blockIdx.y, both directions and four
-// fragments to a block in blockIdx.z (with one block per unit and direction the 12
+// Tables of one frame (blockIdx.x), one unit per blockIdx.y, the directions that have a
+// table and four fragments to a block in blockIdx.z (with one block per unit and direction the 12
 // frames of a 700 x 800 job took 28 us in FP32, 64 us in the banded form): lane
 // (m, gq) of a fragment holds T[m][window row, column 8 gq + e] of its part (see
 // em_cell.h); direction 0: g = f flipped (forward), 1: g = f; f zero-padded from K
@@ -269,7 +269,9 @@ __global__ __launch_bounds__(256) void cell_table_kernel(const float* psf, int K
                                                          unsigned short* tab_fwd,
                                                          unsigned short* tab_adj) {
   const int t = blockIdx.x, unit = blockIdx.y, E = unit / F::NU, u = unit % F::NU;
-  const int dir = blockIdx.z & 1, frag = 4 * (blockIdx.z >> 1) + (threadIdx.x >> 6);
+  const bool both = tab_fwd != nullptr && tab_adj != nullptr;
+  const int dir = both ? blockIdx.z & 1 : tab_fwd == nullptr;
+  const int frag = 4 * (both ? blockIdx.z >> 1 : blockIdx.z) + (threadIdx.x >> 6);
   if (frag >= F::NFU) return;
   unsigned short* tab = dir == 0 ? tab_fwd : tab_adj;
   const int off = (CELL_K - K) / 2;
@@ -356,7 +358,8 @@ hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd
                               bool lo_band, hipStream_t s) {
   auto go = [&](auto form) {
     using F = decltype(form);
-    hipLaunchKernelGGL(cell_table_kernel<F>, dim3(g.n, F::UPF, 2 * ((F::NFU + 3) / 4)), dim3(256), 0, s, psf,
+    const int dirs = (tab_fwd != nullptr) + (tab_adj != nullptr);
+    hipLaunchKernelGGL(cell_table_kernel<F>, dim3(g.n, F::UPF, dirs * ((F::NFU + 3) / 4)), dim3(256), 0, s, psf,
                        g.K, static_cast<unsigned short*>(tab_fwd), static_cast<unsigned short*>(tab_adj));
   };
   if (g.precision == EM_FP32) go(CellForm<EM_FP32, false>{});

@@ -488,10 +488,12 @@ size_t cell2_table_bytes(int n, int dir) {
 
 hipError_t launch_cell2_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                                hipStream_t s) {
-  hipLaunchKernelGGL(cell2_fwd_table_kernel<Fwd2::F>, dim3((g.n + CELL2_FQ - 1) / CELL2_FQ, Fwd2::F::UPF, (Fwd2::F::NFU + 3) / 4),
-                     dim3(256), 0, s, psf, g.n, g.K, static_cast<unsigned short*>(tab_fwd));
-  hipLaunchKernelGGL(cell2_adj_table_kernel<Adj2>, dim3(g.n, 2, (Adj2::NF + 3) / 4), dim3(256), 0, s, psf, g.K,
-                     static_cast<unsigned short*>(tab_adj));
+  if (tab_fwd != nullptr)
+    hipLaunchKernelGGL(cell2_fwd_table_kernel<Fwd2::F>, dim3((g.n + CELL2_FQ - 1) / CELL2_FQ, Fwd2::F::UPF, (Fwd2::F::NFU + 3) / 4),
+                       dim3(256), 0, s, psf, g.n, g.K, static_cast<unsigned short*>(tab_fwd));
+  if (tab_adj != nullptr)
+    hipLaunchKernelGGL(cell2_adj_table_kernel<Adj2>, dim3(g.n, 2, (Adj2::NF + 3) / 4), dim3(256), 0, s, psf, g.K,
+                       static_cast<unsigned short*>(tab_adj));
   return hipGetLastError();
 }
 

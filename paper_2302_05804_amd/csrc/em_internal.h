@@ -278,6 +278,7 @@ hipError_t launch_adjoint_batched(int sr, int KT, const AdjLaunch* descs, const 
 int mfma_variants();
 // whether the variants of a direction (0 forward, 1 adjoint) are different kernels
 bool mfma_has_variants(const Geometry& g, int dir);
+// the tables of both directions; nullptr: not that direction's
 hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
                               hipStream_t s, bool lo_band = false);
 int mfma_tile_h(const Geometry& g, int dir);   // outputs of a workgroup, sr = 1

@@ -865,6 +865,7 @@ hipError_t launch_mfma_tables(const Geometry& g, const float* psf, void* tab_fwd
   dim3 grid(g.n, KTP);
   for (int dir = 0; dir < 2; ++dir) {
     unsigned short* t = static_cast<unsigned short*>(dir == 0 ? tab_fwd : tab_adj);
+    if (t == nullptr) continue;
     if (g.precision == EM_FP16_SPLIT)
       hipLaunchKernelGGL(mfma_table_kernel<EM_FP16_SPLIT>, grid, dim3(256), 0, s, psf, g.n, g.K,
                          g.KT, KTP, dir, t);

@@ -850,15 +850,16 @@ hipError_t launch_mfma2_tables(const Geometry& g, const float* psf, void* tab_fw
                                hipStream_t s) {
   auto ker = g.precision == EM_FP16_SPLIT ? m2_table_kernel<EM_FP16_SPLIT>
                                           : m2_table_kernel<EM_BF16_SPLIT>;
-  if (uses_m2n(g)) {
+  if (tab_fwd != nullptr && uses_m2n(g)) {
     const hipError_t e = launch_mfma2n_table(g, psf, tab_fwd, s);
     if (e != hipSuccess) return e;
-  } else {
+  } else if (tab_fwd != nullptr) {
     hipLaunchKernelGGL(ker, dim3(g.n, M2_FROWS), dim3(384), 0, s, psf, g.n, g.K, 0,
                        static_cast<unsigned short*>(tab_fwd));
   }
-  hipLaunchKernelGGL(ker, dim3(g.n, 2 * M2_AROWS), dim3(384), 0, s, psf, g.n, g.K, 1,
-                     static_cast<unsigned short*>(tab_adj));
+  if (tab_adj != nullptr)
+    hipLaunchKernelGGL(ker, dim3(g.n, 2 * M2_AROWS), dim3(384), 0, s, psf, g.n, g.K, 1,
+                       static_cast<unsigned short*>(tab_adj));
   return hipGetLastError();
 }
 
