@@ -99,10 +99,11 @@ def kernel_sources_sha(prec: str, sr: int = 1) -> str:
     return h.hexdigest()[:16]
 
 
-def recorded_traffic(kernel: str, workload: str, prec: str, sr: int):
+def recorded_traffic(kernel: str, workload: str, prec: str, sr: int, variant: int = 0, path=None):
     """HBM bytes per launch from committed rocprofv3 --pmc summaries, scaled by the
-    copy-kernel calibration; None if absent or taken on other kernel sources."""
-    path = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
+    copy-kernel calibration; None if absent or taken on other kernel sources or with
+    another kernel variant than `variant`."""
+    path = path or os.path.join(ROOT, "profiles", "hbm_traffic.txt")
     if not os.path.exists(path):
         return None
     sha = kernel_sources_sha(prec, sr)
@@ -112,7 +113,7 @@ def recorded_traffic(kernel: str, workload: str, prec: str, sr: int):
         if not line or line.startswith("#"):
             continue
         fields = dict(kv.split("=", 1) for kv in line.split() if "=" in kv)
-        if fields.get("kernel") == key and fields.get("sources") == sha:
+        if (fields.get("kernel"), fields.get("sources"), fields.get("tuned")) == (key, sha, str(variant)):
             return float(fields["bytes_per_launch"])
     return None
 
@@ -260,7 +261,8 @@ def time_form(em, prob, tensors, prec_name, steps, warmup, stream, nu=0.0, job_i
         "roofline": {"bound": "mfma" if mf else "alu", "kernel": name,
                      "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(achieved / peak, 4),
-                     "traffic": recorded_traffic(name, prob.name, prec_name, prob.sr)},
+                     "traffic": recorded_traffic(name, prob.name, prec_name, prob.sr,
+                                                 tuned.get(f"{name}_variant", 0) if tuned else 0)},
     }
 
 
