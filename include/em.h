@@ -72,8 +72,9 @@ extern "C" {
                                served: on the matrix cores, each operand as
                                the exact sum of three bf16 parts, eight of
                                their nine products (the ninth is below 2^-32 of
-                               the whole one), summed in FP32 in levels.  All
-                               else: direct convolution                        */
+                               the whole one), summed in FP32 in levels and over
+                               the frames of the adjoint in FP64.  All else:
+                               direct convolution                              */
 #define EM_BF16_SPLIT  1    /* BF16 MFMA, image and PSF split into hi+lo,
                                three products (hi hi, hi lo, lo hi), FP32
                                accumulation.  K = 43, sr = 1, not served: when
@@ -238,9 +239,9 @@ int em_set_variants(em_ctx* ctx, int32_t fwd_variant, int32_t adj_variant);
  * job's own data (n_rep launches each, the variants in turn, after one turn of
  * warm-up; HIP events on the job's stream; the iterate x is not modified) and
  * selects the fastest for ctx alone; variant 0, with one time for all, where a
- * direction has one kernel.  Every job starts on variants 0 / 0, whatever other jobs of the
- * process chose, so its arithmetic never depends on them.  Writes the chosen
- * variants and, if ms != NULL, the mean launch times
+ * direction has one kernel.  Every job starts on variants 0 / 0, whatever other
+ * jobs of the process chose, so its arithmetic never depends on them.  Writes
+ * the chosen variants and, if ms != NULL, the mean launch times
  * ms[dir * em_variant_count() + v].  Synchronous.
  * EM_ENOTSUP for FP32 (one variant).
  */
@@ -271,9 +272,11 @@ int em_destroy(em_ctx* ctx);
  * creates no em_ctx; the caller passes y, v, psf, x0 (or NULL for the flat
  * start) and x exactly as for em_init.  Results are those of em_init +
  * em_iterate with the default kernel variants.
- * Limits: EM_ENOMEM when em_workspace_bytes(p) > EM_NOALLOC_SCRATCH_BYTES (an
- * EM_FP32 problem whose matrix-core tables alone take it beyond runs the direct
- * convolution instead).
+ * Limits: EM_ENOMEM when the workspace of problem p does not fit into
+ * EM_NOALLOC_SCRATCH_BYTES.  Where em_workspace_bytes(p) is beyond it, the call
+ * takes a smaller plan if that one fits: EM_FP32 then runs the direct convolution
+ * in place of the matrix cores, EM_FP16_SPLIT (sr = 1) its 128 x 128 tiles, and the
+ * results agree with em_init's to the rounding of the form.
  * One array per GPU: calls are serialised inside the library and each one
  * synchronises `stream` before returning, so the next call may reuse the
  * array; work of the caller that overlaps a call on the same GPU must not
@@ -313,8 +316,9 @@ int em_adjoint_op(const em_problem* p, const float* psf, const float* r, float* 
  *   y_up, v_up: device n x (factor frame_h) x (factor frame_w), written.
  * factor: 2, 3 or 4.  EM_EINVAL for NULL pointers, buffers that do not fit in
  * their device allocation, non-positive sizes or another factor (a buffer
- * carved out of a larger allocation is checked against that allocation).  Asynchronous on `stream` (hipStream_t as void*,
- * NULL = default stream); allocates nothing.
+ * carved out of a larger allocation is checked against that allocation).
+ * Asynchronous on `stream` (hipStream_t as void*, NULL = default stream);
+ * allocates nothing.
  */
 int em_upsample(int32_t n_frames, int32_t frame_h, int32_t frame_w, int32_t factor,
                 const float* y, const float* v, float* y_up, float* v_up, void* stream);

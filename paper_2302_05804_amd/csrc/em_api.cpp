@@ -134,7 +134,7 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   g->weight_mode = p->weight_mode;
   g->nu = p->weight_mode == EM_W_STUDENT_T ? p->nu : 0.f;
   // FP32 on the matrix cores: from 128 x 128 latent pixels on (below, the tables of
-  // a frame, 432 KB for sr = 1 and 108 KB for sr = 2, would be most of the workspace)
+  // a frame, 480 KiB for sr = 1 and 114 KiB for sr = 2, would be most of the workspace)
   g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->Nl >= 128 * 128;
   g->lean = 0;
   g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 ? small_tiles16(*g) : 0;
@@ -220,7 +220,7 @@ Plan make_plan(const Geometry& g) {
     const bool large_job = (int64_t)g.n * g.Nf * 8 > (int64_t)EM_NOALLOC_SCRATCH_BYTES;
     const int most = g.mc32 ? g.n : large_job ? std::min(g.n, 16) : pl.adj_groups;
     // 8 bytes per pixel of a tile at 4 TB/s against a frame's products of a tile:
-    // 128 x 128 in 18 us (BF16 split), 64 x 128 in 27 us (FP32), in 7 us for sr = 2
+    // 128 x 128 in 18 us (BF16 split), 64 x 128 in 27 us or more (FP32), in 7 us for sr = 2
     const double plane = g.sr == 2 ? 0.0024 : g.mc32 ? 0.0006 : 0.0018;
     pl.adj_fpg = (int)cdiv(g.n, cell_groups(pl.adj_tiles, g.n, 0.3, plane, most));
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
@@ -359,7 +359,7 @@ void em_bind_views(em_ctx* c) {
 extern "C" {
 
 const char* em_version(void) {
-  return "libem 0.1 (gfx950; FP32 direct convolution; FP64 reductions)";
+  return "libem 0.1 (gfx950; FP32, BF16 split and FP16 split convolutions; FP64 reductions)";
 }
 
 const char* em_last_error(void) { return em::g_last_error.c_str(); }

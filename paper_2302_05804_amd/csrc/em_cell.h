@@ -21,14 +21,21 @@
 // each by the table fragments of the j = s - g that its cell rows g need.  A
 // table fragment is read from LDS once per class and wave, at step j, and stays
 // in registers for the G steps that use it; so LDS serves 2 (image) fragments
-// per step and NB * 18 table fragments per class for up to 27 G products.
+// per step and NB * 18 table fragments per class for 18 G (BF16), 54 G (BF16 split; 37 G
+// with its band) or 144 G (FP32) products.
 //
 // Bound by the matrix cores (at the clock they hold under this load): 33 x 2048^2
-// in FP32 issues 3.7 PFLOP of products per launch, forward 2.24 ms = 1.64 PFLOP/s,
-// adjoint 2.48 ms (the r tile is staged anew for every frame); the direct FP32
+// in FP32 issues 5.0 TFLOP of products per launch, forward 2.75 ms = 1.8 PFLOP/s,
+// adjoint 2.96 ms (the r tile is staged anew for every frame); the direct FP32
 // convolution took 7.35 and 7.62 ms.  BF16 split on 33 x 1999 x 2111: forward 1.41
-// -> 1.18 ms, adjoint 2.17 -> 1.01 ms against one-dimensional Toeplitz operands
+// -> 1.18 ms, adjoint 2.17 -> 1.04 ms against one-dimensional Toeplitz operands
 // (alone on the card; 272 tiles in one frame group, two rounds, took 1.77 ms).
+//
+// Sums on the matrix cores: a lane group's eight products are added with what is below
+// 2^-24 of the largest of them cut off, then the four groups and the accumulator one
+// after the other with round to nearest even.  Products of bf16 parts have 16 bits, so
+// that nothing is cut off within 2^-9 of the largest; beside a bright pixel sums come
+// out low by a few 1e-8.
 //
 // FP32 parts: a value times 2^16 is hi + mid + lo, each the bf16 nearest to what is
 // left.  With that factor the last bit of every binary32 number, 2^-149, is a bf16

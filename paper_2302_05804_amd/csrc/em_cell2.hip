@@ -24,8 +24,8 @@
 // (read once from LDS) serve j = 0, 4 and 8 of three of its cell rows; the 9
 // table fragments of a class and part stay in registers.
 //
-// 9 x 701 x 1022 frames: forward 0.36 -> 0.225 ms, adjoint 0.27 -> 0.172 ms against
-// the direct convolution, both near 1.0 PFLOP/s of issued products (two rounds of
+// 9 x 701 x 1022 frames: forward 0.36 -> 0.243 ms, adjoint 0.27 -> 0.180 ms against
+// the direct convolution, both near 1.2 PFLOP/s of issued products (two rounds of
 // tiles on 256 compute units, three of twelve frame slots empty in the forward).
 #include "em_cell.h"
 
@@ -93,8 +93,7 @@ __device__ inline float cell2_direct_adj(const float* __restrict__ taps, const f
 // forward
 // ---------------------------------------------------------------------------
 
-template <int PREC>
-using Fwd2Of = CellCfg<CellForm<PREC, false>, PREC == EM_FP32 ? 4 : 8, 4, 2>;
+using Fwd2 = CellCfg<CellForm<EM_FP32, false>, 4, 4, 2>;
 
 // Two consecutive frame pixels (columns clamped into the frame when not vec).
 __device__ inline f32x2 load2(const float* __restrict__ p, int row, int col, int H, int W, bool vec) {
@@ -254,11 +253,11 @@ __global__ __launch_bounds__(256) void cell2_fwd_table_kernel(const float* psf, 
 // ---------------------------------------------------------------------------
 
 // G cell rows per wave, every fourth one (4 waves), WC waves across.
-template <int PREC_, int G_, int WC_>
+template <int G_, int WC_>
 struct Adj2Cfg {
-  using P = Prec<PREC_>;
+  using P = Prec<EM_FP32>;
   using frag = typename P::frag;
-  static constexpr int PREC = PREC_, G = G_, WC = WC_;
+  static constexpr int G = G_, WC = WC_;
   static constexpr int NA = P::NA, NB = P::NB, NP = P::NP;
   static constexpr int NW = 4 * WC, NT = 64 * NW;
   static constexpr int TH = 16 * G, TW = 64 * WC;        // latent pixels
@@ -317,7 +316,7 @@ struct Adj2Tile {
       } else if (e < C::PLANE) {
         const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
         uint32_t q[C::NB];
-        cell_split2<C::PREC>(f32x2{in ? v[k] * up : 0.f, 0.f}, q);
+        cell_split2<EM_FP32>(f32x2{in ? v[k] * up : 0.f, 0.f}, q);
 #pragma unroll
         for (int p = 0; p < C::NA; ++p) sh[p * C::PLANE + e] = (unsigned short)q[p];
       }
@@ -458,7 +457,7 @@ __global__ __launch_bounds__(256) void cell2_adj_table_kernel(const float* psf, 
     const int ka = 2 * d - (m >> 2), kb = 2 * (8 * (o % 3) + e) - (m & 3);
     float gv = 0.f;
     if (ka >= 0 && ka < CELL2_KC && kb >= 0 && kb < CELL2_KC) gv = box_kernel(h, K, ka, kb);
-    dst[e] = cell_part<C::PREC>(gv, part);
+    dst[e] = cell_part<EM_FP32>(gv, part);
   }
 }
 
@@ -471,8 +470,7 @@ __global__ __launch_bounds__(C::NT) void cell2_adj_kernel(MfmaLaunch a) {
   cell2_adj_body<C>(a, blockIdx.x, blockIdx.y);
 }
 
-using Fwd2 = Fwd2Of<EM_FP32>;
-using Adj2 = Adj2Cfg<EM_FP32, 4, 2>;
+using Adj2 = Adj2Cfg<4, 2>;
 
 }  // namespace
 

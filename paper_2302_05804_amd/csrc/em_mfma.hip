@@ -927,6 +927,8 @@ struct MfVariants {
 // FP16 split on small images: 64 x 64 outputs per workgroup, 8 waves of 2x1
 // blocks.  A job of few tiles is a chain of short launches that each leave most
 // compute units idle; a quarter of the work per wave shortens every one of them.
+// The sums are those of the large tiles; a tile is scaled by its own largest value,
+// so that pixels below 2^-29 of a large tile's may be rounded less in a small one.
 template <int KT>
 hipError_t launch_small(int dir, dim3 grid, const MfmaLaunch& a, hipStream_t s) {
   using C = MfCfg<KT, EM_FP16_SPLIT, 2, 1, 2, 4, 0, 2>;
