@@ -83,8 +83,9 @@ KERNEL_FILES = {
     ("fp16split", 1): ["em_mfma.hip", "em_mfma_common.h", "em_device.h"],
     ("fp32", 2): ["em_cell2.hip", "em_cell.h", "em_mfma_common.h", "em_device.h"],
 }
+KERNEL_FILES[("bf16", 1)] = KERNEL_FILES[("fp16split", 1)]
 KERNEL_FILES.update({(prec, 1): ["em_cell.hip", "em_cell.h", "em_mfma_common.h", "em_device.h"]
-                     for prec in ("fp32", "bf16split", "bf16")})
+                     for prec in ("fp32", "bf16split")})
 KERNEL_FILES.update({(prec, 2): ["em_mfma2.hip", "em_mfma2n.hip", "em_mfma_common.h", "em_device.h"]
                      for prec in ("fp16split", "bf16split", "bf16")})
 

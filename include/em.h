@@ -228,8 +228,8 @@ int em_profile(em_ctx* ctx, int32_t n_iter, double* phase_ms);
  * rounding level).  em_variant_count() gives their number; em_set_variants
  * selects one per direction (0 = forward, 1 = adjoint) for ctx.  Some jobs have
  * one kernel for all variants of a direction, where the choice has no effect:
- * BF16 and BF16 split with sr = 1 and K > 15, and FP16 split with sr = 1 where
- * the image is small.  EM_ENOTSUP for FP32.
+ * BF16 split with sr = 1 and K > 15, and FP16 split with sr = 1 where the image
+ * is small.  EM_ENOTSUP for FP32.
  */
 int em_variant_count(void);
 int em_set_variants(em_ctx* ctx, int32_t fwd_variant, int32_t adj_variant);

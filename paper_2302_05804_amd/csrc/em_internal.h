@@ -98,7 +98,7 @@ inline bool uses_mfma(const Geometry& g) {
 }
 // sr = 1 jobs on the 4 x 4 cell kernels (em_cell.hip)
 inline bool uses_cell(const Geometry& g) {
-  return g.sr == 1 && g.KT == KT_LARGE && uses_mfma(g) && g.precision != EM_FP16_SPLIT;
+  return g.sr == 1 && g.KT == KT_LARGE && (g.precision == EM_BF16_SPLIT || g.mc32 != 0);
 }
 
 bool make_geometry(const void* problem, Geometry* g, const char** why);

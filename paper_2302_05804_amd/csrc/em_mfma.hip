@@ -13,10 +13,10 @@
 // p-values of a column of U_a are non-zero.
 //
 // Precision (template argument PREC, encodings in em_mfma_common.h): bf16 hi +
-// lo split of both operands with three products (EM_BF16_SPLIT) and plain bf16
-// (EM_BF16), both for kernels padded to 15 (43: em_cell.hip), or a binary16 image operand with a per-tile power-of-two scale
-// times a binary16 hi + lo PSF with a per-frame scale, two products
-// (EM_FP16_SPLIT).  Accumulation is FP32 in the matrix core throughout.
+// lo split of both operands with three products (EM_BF16_SPLIT, for kernels padded to
+// 15; 43: em_cell.hip), plain bf16 (EM_BF16), or a binary16 image operand with a
+// per-tile power-of-two scale times a binary16 hi + lo PSF with a per-frame scale, two
+// products (EM_FP16_SPLIT).  Accumulation is FP32 in the matrix core throughout.
 //
 // Data movement (per workgroup of 4 waves, 128 x 128 outputs, each wave 64 x 64
 // = 4 x 4 blocks of 16 x 16):
@@ -1037,11 +1037,13 @@ hipError_t launch_mfma_batched(int KT, int precision, int dir, int variant, cons
     default:                                                                                 \
       return hipErrorInvalidValue;                                                           \
   }
-  if (KT == KT_LARGE && precision != EM_FP16_SPLIT)
-    return r16 ? hipErrorInvalidValue
-               : launch_cell_batched(precision, dir, descs, items, n_items, grid, s, robust);
+  if (KT == KT_LARGE && precision == EM_BF16)
+    return launch_dir_batched<KT_LARGE, EM_BF16>(dir, variant, grid, descs, items, n_items, s, robust, r16);
   if (KT == KT_LARGE && precision == EM_FP16_SPLIT)
     return launch_dir_batched<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, descs, items, n_items, s, robust, r16);
+  if (KT == KT_LARGE)
+    return r16 ? hipErrorInvalidValue
+               : launch_cell_batched(precision, dir, descs, items, n_items, grid, s, robust);
   EM_MF_DISPATCH(KT_SMALL)
 #undef EM_MF_DISPATCH
 }
@@ -1277,6 +1279,7 @@ hipError_t launch_mfma(const Geometry& g, int dir, int variant, int tiles, int g
     return g.KT == KT_LARGE ? launch_small<KT_LARGE>(dir, grid, a, s) : launch_small<KT_SMALL>(dir, grid, a, s);
   if (g.KT == KT_LARGE)
     return g.precision == EM_FP16_SPLIT ? launch_dir<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, a, s)
+           : g.precision == EM_BF16     ? launch_dir<KT_LARGE, EM_BF16>(dir, variant, grid, a, s)
                                         : hipErrorInvalidValue;
   EM_MF_DISPATCH(KT_SMALL)
 #undef EM_MF_DISPATCH

@@ -27,7 +27,7 @@ def _context(prec, h, w, n, K, seed, x0):
 
 
 @pytest.mark.parametrize("prec,h,w,K", [
-    ("BF16_SPLIT", 260, 300, 43), ("BF16", 140, 130, 25),   # 4 x 4 cells
+    ("BF16_SPLIT", 260, 300, 43), ("BF16_SPLIT", 140, 130, 25),   # 4 x 4 cells
     ("FP16_SPLIT", 96, 96, 43), ("FP16_SPLIT", 64, 200, 15),   # 64 x 64 tiles
 ])
 def test_one_kernel_is_variant_0(prec, h, w, K):
@@ -38,10 +38,10 @@ def test_one_kernel_is_variant_0(prec, h, w, K):
     assert (f, a) == (0, 0) and (ms > 0).all() and (ms == ms[:, :1]).all()
 
 
-@pytest.mark.parametrize("prec", ["BF16_SPLIT", "BF16"])
-def test_small_kernel_variants_match_oracle(prec):
-    """K <= 15: three layouts of the two-plane and one-plane forms, in both directions."""
-    h, w, K = 260, 300, 15
+@pytest.mark.parametrize("prec,K", [("BF16_SPLIT", 15), ("BF16", 15), ("BF16", 43)])
+def test_bf16_variants_match_oracle(prec, K):
+    """Three layouts of the two-plane (K <= 15) and one-plane forms, in both directions."""
+    h, w = 260, 300
     x0 = synth.positive_start((h, w), 5.0, seed=43)
     outs = []
     for fv in range(3):
@@ -57,7 +57,7 @@ def test_small_kernel_variants_match_oracle(prec):
             ctx.close()
     xo = oracle.run(p.y, p.v, p.psf, x0, 4)
     errs = [rel_l2(o, xo) for o in outs]
-    log(f"{prec} K=15: rel L2 {min(errs):.2e} .. {max(errs):.2e}")
+    log(f"{prec} K={K}: rel L2 {min(errs):.2e} .. {max(errs):.2e}")
     # split form: 1e-4; plain BF16: 2^-9 per operand, four iterations
     assert max(errs) <= (1e-4 if prec == "BF16_SPLIT" else 4 * 2.0 ** -8)
 
