@@ -47,19 +47,41 @@ int fail(int code, const char* fmt, ...) {
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Time, in frames, of a launch of `tiles` tiles by groups of fpg frames (the last one
+// has what is left) on `slots` workgroups resident, each of which takes its frames
+// plus `fixed` (its set-up): the groups follow one another, and a free slot takes the
+// next workgroup.
+static double launch_span(int64_t tiles, int n, int64_t fpg, int slots, double fixed) {
+  const int64_t groups = cdiv(n, fpg), full = (groups - 1) * tiles, r = full % slots;
+  const double a = (double)fpg + fixed, b = (double)(n - (groups - 1) * fpg) + fixed;
+  // the last group's workgroups, on the slots that are free now and on the r others
+  double now = (double)(full / slots) * a, later = now + a, end = r ? later : now;
+  for (int64_t left = tiles; left > 0;) {
+    double& t = r == 0 || now <= later ? now : later;
+    left -= &t == &now ? slots - r : r;
+    t += b;
+    end = std::max(end, t);
+  }
+  return end;
+}
+
 // Frame groups of a launch that has `slots` workgroups resident: the count whose
 // rounds over them, times a workgroup's frames plus `fixed` (its set-up, in frames),
 // take the least time.  `plane`: what writing and reading one tile of a partial plane
-// takes, in frames times compute units (none with one group).
-static int cell_groups(int tiles, int n, double fixed, double plane, int most, int slots = 256,
-                       double* least = nullptr) {
+// takes, in frames times compute units (none with one group).  `span`: by launch_span,
+// which knows that the last group may be shorter (15 frames of 65 tiles as 8 groups
+// end after two rounds of two frames, not three); the cell kernels' counts, which fix
+// the order of their frame sum, are those of whole rounds.
+static int frame_groups(int tiles, int n, double fixed, double plane, int most, int slots = 256,
+                        bool span = false, double* least = nullptr) {
   int best = 1;
   double cost = 1e300;
   const int last = std::min(std::min(n, most), 1024);   // beyond, the rounds differ by little
   for (int g = 1; g <= last; ++g) {
     const int64_t fpg = cdiv(n, g), groups = cdiv(n, fpg);
-    const double c = (double)cdiv((int64_t)tiles * groups, slots) * ((double)fpg + fixed) +
-                     (groups > 1 ? plane * (double)groups * tiles : 0.0);
+    const double c = span ? launch_span(tiles, n, fpg, slots, fixed)
+                          : (double)cdiv((int64_t)tiles * groups, slots) * ((double)fpg + fixed) +
+                                (groups > 1 ? plane * (double)groups * tiles : 0.0);
     if (c < 0.98 * cost) {
       cost = c;
       best = (int)groups;
@@ -78,24 +100,29 @@ static int adjoint_groups(int tiles, int n) {
 }
 
 // FP16 split, sr = 1: tiles of 128 x 128 outputs (one workgroup to a compute unit) or
-// of 64 x 64 (two).  Forward (its groups are free): a frame takes 27 us in a large
-// tile and 17.5 us in each of two small ones; small ones from a gain of 7 % on (us,
-// large / small: 25 x 500 x 400 64 / 57, 6 x 900 x 700 61 / 41, 33 x 400 x 500 86 / 71;
-// 16 x 640^2 63 / 75, 20 x 1000 x 300 65 / 80, 10 x 1024^2 90 / 93).  Adjoint (its
-// groups are those of the large tiles): a small tile is a quarter of the work at 1 / f
-// of the efficiency, f = 1.4 on binary16 r planes (12 x 1500 x 1777, 168 large tiles:
-// 282 against 311 us; 33 x 1999 x 2111, 272: 1396 against 1186 us), 1.8 where it
-// stages FP32 r (342 against 499 us).
+// of 64 x 64 (two).  Forward (its groups are free): a round of small tiles takes 0.63
+// of a round of large ones (1024 x 4096, 6 frames: 2 rounds 88 us each against 145 us);
+// small ones from a gain of 5 % on (us per launch, large / small: 25 x 500 x 400 64 /
+// 57, 6 x 900 x 700 61 / 41, 33 x 400 x 500 86 / 71; 16 x 640^2 63 / 75, 20 x 1000 x 300
+// 65 / 80).  Adjoint (its groups are those of the large tiles): a small tile is a
+// quarter of the work at 1 / f of the efficiency.  f = 1.4 on binary16 r planes, whose
+// staged rows a small tile re-reads (12 x 1500 x 1777, 168 large tiles: 282 against
+// 311 us; 33 x 1999 x 2111, 272: 1396 against 1186 us).  f = 2.1 where it stages FP32 r
+// in registers: one small workgroup to a compute unit, so that small tiles gain in one
+// round of them (us per iteration, large / small: 29 x 105 x 70 with 116 small tiles
+// 106 / 86; 16 x 891 x 114, 448: 112 / 117; 23 x 375 x 255, 552: 117 / 152); 1.8 for
+// kernels padded to 15, with two to a compute unit (18 x 104 x 461: 70 / 61).
 static constexpr int SMALL16_SLOTS = 512;
 static int small_tiles16(const Geometry& g) {
   const int big = (int)(cdiv(g.Hf, 128) * cdiv(g.Wf, 128)), small = (int)(cdiv(g.Hf, 64) * cdiv(g.Wf, 64));
   double cb, cs;
-  (void)cell_groups(big, g.n, 0.3, 0.0, g.n, 256, &cb);
-  (void)cell_groups(small, g.n, 0.3, 0.0, g.n, SMALL16_SLOTS, &cs);
-  const int64_t G = adjoint_groups(big, g.n);
-  const double f = g.weight_mode == EM_W_ADJOINT ? 1.4 : 1.8;
-  return (cs * 0.7 < cb ? SMALL16_FWD : 0) |
-         ((double)cdiv(small * G, 256) * 0.25 * f < (double)cdiv(big * G, 256) ? SMALL16_ADJ : 0);
+  (void)frame_groups(big, g.n, 0.3, 0.0, g.n, 256, true, &cb);
+  (void)frame_groups(small, g.n, 0.3, 0.0, g.n, SMALL16_SLOTS, true, &cs);
+  const int64_t fpg = cdiv(g.n, adjoint_groups(big, g.n));
+  const double f = g.weight_mode == EM_W_ADJOINT ? 1.4 : g.KT == KT_LARGE ? 2.1 : 1.8;
+  return (cs * 0.66 < cb ? SMALL16_FWD : 0) |
+         (launch_span(small, g.n, fpg, 256, 0.3) * 0.25 * f < launch_span(big, g.n, fpg, 256, 0.3) ? SMALL16_ADJ
+                                                                                                : 0);
 }
 
 bool make_geometry(const void* problem, Geometry* g, const char** why) {
@@ -183,11 +210,12 @@ Plan make_plan(const Geometry& g) {
   const int old = (large ? large : pl.fwd_tiles) * (int)cdiv(g.n, pl.fwd_fpg);
   const int room = std::max(1, std::max(g.lean ? 0 : pl.prep_blocks, old) / pl.fwd_tiles);
   if (uses_cell(g) || (g.sr == 1 && g.precision == EM_FP16_SPLIT))
-    pl.fwd_fpg = (int)cdiv(g.n, cell_groups(pl.fwd_tiles, g.n, 0.3, 0.0, room,
-                                            g.small16 & SMALL16_FWD ? SMALL16_SLOTS : 256));
+    pl.fwd_fpg = (int)cdiv(g.n, frame_groups(pl.fwd_tiles, g.n, 0.3, 0.0, room,
+                                             g.small16 & SMALL16_FWD ? SMALL16_SLOTS : 256,
+                                             g.precision == EM_FP16_SPLIT));
   if (uses_cell2(g)) {   // four frames to a product
     const int quads = (int)cdiv(g.n, 4);
-    pl.fwd_fpg = 4 * (int)cdiv(quads, cell_groups(pl.fwd_tiles, quads, 0.3, 0.0, room));
+    pl.fwd_fpg = 4 * (int)cdiv(quads, frame_groups(pl.fwd_tiles, quads, 0.3, 0.0, room));
   }
   if (uses_m2n(g)) pl.fwd_fpg = M2N_FPG;   // the frames are the products' N dimension
   pl.fwd_groups = (int)cdiv(g.n, pl.fwd_fpg);
@@ -222,7 +250,7 @@ Plan make_plan(const Geometry& g) {
     // 8 bytes per pixel of a tile at 4 TB/s against a frame's products of a tile:
     // 128 x 128 in 18 us (BF16 split), 64 x 128 in 27 us or more (FP32), in 7 us for sr = 2
     const double plane = g.sr == 2 ? 0.0024 : g.mc32 ? 0.0006 : 0.0018;
-    pl.adj_fpg = (int)cdiv(g.n, cell_groups(pl.adj_tiles, g.n, 0.3, plane, most));
+    pl.adj_fpg = (int)cdiv(g.n, frame_groups(pl.adj_tiles, g.n, 0.3, plane, most));
     pl.adj_groups = (int)cdiv(g.n, pl.adj_fpg);
   }
   if (g.weight_mode == EM_W_LITERAL) {
