@@ -1096,8 +1096,8 @@ int em_autotune(em_ctx* c, int32_t n_rep, int32_t* fwd_variant, int32_t* adj_var
     int row = 1;
     for (int k = 0; k <= n_rep && e == hipSuccess; ++k) {
       float longest = 0.f;
-      // ahead of the first one as of the others: a launch of another variant
-      e = launch_mfma(c->g, dir, nd - 1, tiles, groups, m, c->stream);
+      // short launches: ahead of the first row, as of the others, one of another variant
+      if (row > 1) e = launch_mfma(c->g, dir, nd - 1, tiles, groups, m, c->stream);
       if (e == hipSuccess) e = hipEventRecord(ev[0], c->stream);
       for (int v = 0; v < nd && e == hipSuccess; ++v) {
         for (int i = 0; i < row && e == hipSuccess; ++i)
