@@ -237,10 +237,10 @@ int em_set_variants(em_ctx* ctx, int32_t fwd_variant, int32_t adj_variant);
 /*
  * Autotuner: times every variant of the forward and the adjoint kernel on the
  * job's own data (n_rep turns of each variant, one launch or a row of short
- * ones, after one turn of warm-up; HIP events on the job's stream; the iterate x is not modified) and
- * selects for ctx alone the fastest (a higher variant where it is 1.5 % faster
- * than a lower one); variant 0, with one time for all, where a direction has one
- * kernel.  Every job starts on variants 0 / 0, whatever other
+ * ones, after one turn of warm-up; HIP events on the job's stream; the iterate x
+ * is not modified) and selects for ctx alone the fastest (a higher variant where
+ * it is 1.5 % faster than a lower one); variant 0, with one time for all, where
+ * a direction has one kernel.  Every job starts on variants 0 / 0, whatever other
  * jobs of the process chose, so its arithmetic never depends on them.  Writes
  * the chosen variants and, if ms != NULL, the mean launch times
  * ms[dir * em_variant_count() + v].  Synchronous.
