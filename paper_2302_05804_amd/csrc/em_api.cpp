@@ -164,6 +164,7 @@ bool make_geometry(const void* problem, Geometry* g, const char** why) {
   // a frame, 480 KiB for sr = 1 and 114 KiB for sr = 2, would be most of the workspace)
   g->mc32 = p->precision == EM_FP32 && g->KT == KT_LARGE && g->Nl >= 128 * 128;
   g->lean = 0;
+  g->served = 0;
   g->small16 = p->precision == EM_FP16_SPLIT && g->sr == 1 ? small_tiles16(*g) : 0;
   g->small32 = p->precision == EM_FP32 && !g->mc32 && g->sr == 1 &&
                cdiv(g->Hf, 64) * cdiv(g->Wf, 64) * g->n <= 256;
@@ -713,7 +714,7 @@ static int setup_job(em_ctx* c, const em_problem* p, const float* y, const float
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
-  if (serving) g.mc32 = g.small16 = g.small32 = 0;
+  if (serving) make_served(&g);
   if (lean) make_lean(&g);
   if (g.weight_mode == EM_W_LITERAL && g.sr != 1)
     return fail(EM_ENOTSUP, "the typeset weighting is defined for sr = 1 only");
@@ -960,7 +961,7 @@ int em_check_plan(const em_problem* p) {
     const bool serving = kind == 2;
     Geometry g = full;
     if (kind == 1) make_lean(&g);
-    if (serving) g.mc32 = g.small16 = g.small32 = 0;
+    if (serving) make_served(&g);
     const Plan pl = serving ? make_serving_plan(g) : make_plan(g);
     em_ctx c{};
     c.g = g;

@@ -22,8 +22,7 @@
 // table fragment is read from LDS once per class and wave, at step j, and stays
 // in registers for the G steps that use it; so LDS serves 2 (image) fragments
 // per step and NB * 18 table fragments per class for 54 G (BF16 split; 37 G with its band)
-// or 144 G (FP32) products.  (Plain BF16, 18 G, has too few of them: it lost up to 10%
-// to one-dimensional Toeplitz operands, 19 x 894 x 1307 228 -> 254 us per iteration.)
+// or 144 G (FP32) products.  (Plain BF16, served jobs only: 18 G.)
 //
 // Bound by the matrix cores (at the clock they hold under this load): 33 x 2048^2
 // in FP32 issues 5.0 TFLOP of products per launch, forward 2.75 ms = 1.8 PFLOP/s,
@@ -451,7 +450,7 @@ __device__ inline int cell_tail_off() {
 // taps, so it makes NaN of every output whose 46 x 48 window holds it.  The outputs
 // that are not finite are formed once more as the direct convolution does, one at a
 // time: `value(g, i)` for element i of cell row g; so are those below `least` (in a
-// tile of the lower factor, whose smallest operands are cut off).  The BF16 split form leaves
+// tile of the lower factor, whose smallest operands are cut off).  The BF16 forms leave
 // them: NaN up to three pixels outside the support (with this step their adjoint
 // spilled: 33 x 1999 x 2111 1.04 -> 1.09 ms).
 template <int G, class Fn>

@@ -1,6 +1,7 @@
 // em_cell.hip -- kernels of one EM iteration on the 4 x 4 cell core of em_cell.h:
 // forward model, weighting and adjoint of Eq. (2) (arXiv:2302.05804, Sec. 2) for
-// sr = 1 and kernels padded to 43 x 43, in the BF16 split form and in FP32.
+// sr = 1 and kernels padded to 43 x 43, in FP32, the BF16 split form and, served, plain
+// BF16.
 #include "em_cell.h"
 
 #include <type_traits>
@@ -325,8 +326,9 @@ static_assert(CellOf<EM_FP32, false>::TW == CELL_TILE_W && CellOf<EM_BF16_SPLIT,
 size_t cell_table_bytes(int n) { return (size_t)n * CellForm<EM_FP32, false>::FRAME * 16; }
 template <class F>
 constexpr bool cell_table_fits = F::FRAME * 16 <= (int64_t)mfma_table_frame(KT_LARGE);
-static_assert(cell_table_fits<CellForm<EM_BF16_SPLIT, false>> && cell_table_fits<CellForm<EM_BF16_SPLIT, true>>,
-              "the BF16 split form's tables within mfma_table_bytes");
+static_assert(cell_table_fits<CellForm<EM_BF16_SPLIT, false>> && cell_table_fits<CellForm<EM_BF16_SPLIT, true>> &&
+                  cell_table_fits<CellForm<EM_BF16, false>>,
+              "the BF16 forms' tables within mfma_table_bytes");
 
 // The BF16 split form takes its band for jobs whose PSFs passed the band check,
 // and not in serving.
@@ -338,6 +340,7 @@ hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, h
     case EM_BF16_SPLIT:
       return a.lo_band ? launch_one<EM_BF16_SPLIT, true>(kind, grid, a, s)
                        : launch_one<EM_BF16_SPLIT, false>(kind, grid, a, s);
+    case EM_BF16: return launch_one<EM_BF16, false>(kind, grid, a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -345,8 +348,11 @@ hipError_t launch_cell(int precision, int dir, dim3 grid, const MfmaLaunch& a, h
 hipError_t launch_cell_batched(int precision, int dir, const MfmaLaunch* descs, const int4* items,
                                int n_items, int grid, hipStream_t s, bool robust) {
   const int kind = dir == 1 ? K_ADJ : robust ? K_FWD_T : K_FWD;
-  if (precision != EM_BF16_SPLIT) return hipErrorInvalidValue;
-  return launch_many<EM_BF16_SPLIT, false>(kind, grid, descs, items, n_items, s);
+  switch (precision) {
+    case EM_BF16_SPLIT: return launch_many<EM_BF16_SPLIT, false>(kind, grid, descs, items, n_items, s);
+    case EM_BF16: return launch_many<EM_BF16, false>(kind, grid, descs, items, n_items, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd, void* tab_adj,
@@ -358,6 +364,7 @@ hipError_t launch_cell_tables(const Geometry& g, const float* psf, void* tab_fwd
                        g.K, static_cast<unsigned short*>(tab_fwd), static_cast<unsigned short*>(tab_adj));
   };
   if (g.precision == EM_FP32) go(CellForm<EM_FP32, false>{});
+  else if (g.precision == EM_BF16) go(CellForm<EM_BF16, false>{});
   else if (lo_band) go(CellForm<EM_BF16_SPLIT, true>{});
   else go(CellForm<EM_BF16_SPLIT, false>{});
   return hipGetLastError();

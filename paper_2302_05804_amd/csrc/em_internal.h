@@ -61,7 +61,14 @@ struct Geometry {
   // tables do not fit (serving arenas, the static scratch)
   int mc32;
   int lean;   // the smallest workspace (em_run_noalloc, where no other fits)
+  int served; // the job of a server (fixed kernel variants, batched launches)
 };
+
+// The geometry of a served job: no FP32 tables of the matrix cores, no small tiles.
+inline void make_served(Geometry* g) {
+  g->mc32 = g->small16 = g->small32 = 0;
+  g->served = 1;
+}
 
 // Launch shape chosen for a geometry (a pure function of the geometry, so the
 // arithmetic of a job never depends on what else runs).
@@ -96,9 +103,13 @@ inline bool uses_mfma(const Geometry& g) {
   return g.precision == EM_BF16_SPLIT || g.precision == EM_FP16_SPLIT || g.precision == EM_BF16 ||
          g.mc32 != 0;
 }
-// sr = 1 jobs on the 4 x 4 cell kernels (em_cell.hip)
+// sr = 1 jobs on the 4 x 4 cell kernels (em_cell.hip).  Plain BF16: served jobs (rounds of
+// 8 jobs of 256 .. 832 squares 87 -> 62 ms against the Toeplitz kernels' fixed variants);
+// alone, the tuned Toeplitz kernels are up to 10% faster (19 x 894 x 1307 228 against
+// 254 us per iteration; others up to 1.2 times slower)
 inline bool uses_cell(const Geometry& g) {
-  return g.sr == 1 && g.KT == KT_LARGE && (g.precision == EM_BF16_SPLIT || g.mc32 != 0);
+  return g.sr == 1 && g.KT == KT_LARGE &&
+         (g.precision == EM_BF16_SPLIT || g.mc32 != 0 || (g.precision == EM_BF16 && g.served != 0));
 }
 
 bool make_geometry(const void* problem, Geometry* g, const char** why);

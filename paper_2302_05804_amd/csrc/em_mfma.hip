@@ -14,7 +14,7 @@
 //
 // Precision (template argument PREC, encodings in em_mfma_common.h): bf16 hi +
 // lo split of both operands with three products (EM_BF16_SPLIT, for kernels padded to
-// 15; 43: em_cell.hip), plain bf16 (EM_BF16), or a binary16 image operand with a
+// 15; 43: em_cell.hip), plain bf16 (EM_BF16; 43, served: em_cell.hip), or a binary16 image operand with a
 // per-tile power-of-two scale times a binary16 hi + lo PSF with a per-frame scale, two
 // products (EM_FP16_SPLIT).  Accumulation is FP32 in the matrix core throughout.
 //
@@ -1037,8 +1037,6 @@ hipError_t launch_mfma_batched(int KT, int precision, int dir, int variant, cons
     default:                                                                                 \
       return hipErrorInvalidValue;                                                           \
   }
-  if (KT == KT_LARGE && precision == EM_BF16)
-    return launch_dir_batched<KT_LARGE, EM_BF16>(dir, variant, grid, descs, items, n_items, s, robust, r16);
   if (KT == KT_LARGE && precision == EM_FP16_SPLIT)
     return launch_dir_batched<KT_LARGE, EM_FP16_SPLIT>(dir, variant, grid, descs, items, n_items, s, robust, r16);
   if (KT == KT_LARGE)

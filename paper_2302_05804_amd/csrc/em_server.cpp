@@ -747,7 +747,7 @@ int em_submit(em_server* S, const em_problem* p, const float* y_host, const floa
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return fail(EM_EINVAL, "invalid problem: %s", why);
-  g.mc32 = g.small16 = g.small32 = 0;   // as setup_job
+  make_served(&g);   // as setup_job
   if (g.weight_mode == EM_W_LITERAL) return fail(EM_ENOTSUP, "weight mode not provided");
   size_t total, a, b, c2, d, e, wsb;
   job_layout(g, &total, &a, &b, &c2, &d, &e, &wsb);
@@ -917,7 +917,7 @@ size_t em_job_bytes(const em_problem* p) {
   Geometry g;
   const char* why = nullptr;
   if (!make_geometry(p, &g, &why)) return 0;
-  g.mc32 = g.small16 = g.small32 = 0;   // as setup_job
+  make_served(&g);   // as setup_job
   size_t total, a, b, c, d, e, w;
   job_layout(g, &total, &a, &b, &c, &d, &e, &w);
   return total;

@@ -135,3 +135,26 @@ def test_noalloc_on_the_smallest_plan():
     err = float((a.double() - b.double()).norm() / b.double().norm())
     log(f"smallest plan: rel L2 {err:.2e}, loglik {np.abs(ta / tb - 1).max():.2e}")
     assert err <= 1e-6 and np.abs(ta / tb - 1).max() <= 1e-7
+
+
+@pytest.mark.parametrize("nu", [0.0, 3.0])
+def test_served_plain_bf16(nu):
+    """Served plain BF16 jobs run on the cells (alone they do not): two jobs of ragged
+    sizes in one round, each against the oracle (2^-9 for each operand, four iterations)."""
+    em = _em()
+    srv = em.Server(256 << 20, max_slots=2)
+    jobs = []
+    for k, (h, w, n, K) in enumerate([(131, 205, 3, 43), (96, 77, 5, 31)]):
+        p = synth.make_problem("c2", H=h, W=w, n=n, K=K, seed=8600 + k)
+        y = synth.add_trails(p.y, p.v, 8700 + k)[0] if nu else p.y
+        jid = srv.submit(em.Problem.make(n, h, w, K, precision=em.BF16, nu=nu), y, p.v, p.psf, 4)
+        jobs.append((p, y, jid))
+    for p, y, jid in jobs:
+        x, ll = srv.wait(jid)
+        x0 = np.full(p.latent_shape, oracle.flat_x0(y, p.v), np.float32)
+        xo = oracle.run_t(y, p.v, p.psf, x0, 4, nu) if nu else oracle.run(y, p.v, p.psf, x0, 4)
+        lo = oracle.loglik_t(y, p.v, p.psf, xo, nu) if nu else oracle.loglik(y, p.v, p.psf, xo)
+        err = rel_l2(x, xo)
+        log(f"served BF16 nu={nu} {y.shape}: x {err:.2e}, loglik {abs(ll / lo - 1):.2e}")
+        assert err <= 4 * 2.0 ** -8 and abs(ll / lo - 1) <= 4 * 2.0 ** -8
+    srv.close()
